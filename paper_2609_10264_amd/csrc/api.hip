@@ -227,7 +227,7 @@ mvk_status server_eval_impl(const int8_t* W, uint32_t m, uint32_t n, const uint3
     }
     void* ws = nullptr;
     uint32_t* ctrl = nullptr;
-    const ServerEvalPlan pl = server_eval_plan(m, n, B, path, packed);
+    const ServerEvalPlan pl = server_eval_plan(m, n, B, path, packed, n % 16 == 0 && (uintptr_t)W % 16 == 0);
     if (pl.ws_bytes || pl.ctrl_words) {
         const mvk_status st = workspace(s, pl.ws_bytes, &ws, &ctrl, kCtrlBase + 4 * pl.ctrl_words);
         if (st) return st;

@@ -203,11 +203,59 @@ inline YOut yout_shift(YOut o, uint32_t b0) {
     return o;
 }
 
+// Loads at the alignment the data has: 16 bytes at any byte (row-major W whose
+// rows are not whole 16-byte granules) and four words at any word (a query row
+// of any length).  The compiler emits one global_load_dwordx4 for either.
+typedef int32_t v4i_b __attribute__((ext_vector_type(4), aligned(1)));
+typedef uint32_t v4u_w __attribute__((ext_vector_type(4), aligned(4)));
+
+// The 16 query elements k0 .. k0+15 of row xr (n elements, zero beyond them
+// and where !ok), in whole words at any word alignment.
+__device__ __forceinline__ void load_x16(uint32_t (&x)[16], const uint32_t* xr, uint32_t k0, uint32_t n, bool ok) {
+    if (ok && k0 + 16 <= n) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const v4u_w t = *reinterpret_cast<const v4u_w*>(xr + k0 + 4 * v);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[4 * v + e] = t[e];
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const bool in = ok && k0 + e < n;
+            const uint32_t t = xr[in ? k0 + e : 0u];
+            x[e] = in ? t : 0u;
+        }
+    }
+}
+
 // 16 bytes of W, a non-temporal load: W is streamed once per launch, so its
 // lines are not kept in the caches (measured on MI355X: the single-query
 // launch at 4096 x 4096 from 5.2 to 4.9 us, at 16384 x 16384 from 46 to 41 us).
 __device__ __forceinline__ v4i load_w16(const int8_t* p) {
     return __builtin_nontemporal_load(reinterpret_cast<const v4i*>(p));
+}
+
+// Row-major W at any alignment and width: a lane's 16 bytes start at byte
+// `off` of the matrix (total = m * n bytes, at least 16) and may run into the
+// next row (those columns meet zero digits) but not past the matrix: the load
+// is moved down to the last 16 bytes, and w16_at shifts what it got back up.
+// Only workgroups that hold the end of the matrix need the shift.
+__device__ __forceinline__ v4i load_w16_any(const int8_t* W, size_t off, size_t total) {
+    return *reinterpret_cast<const v4i_b*>(W + (off + 16 <= total ? off : total - 16));
+}
+__device__ __forceinline__ v4i w16_at(v4i w, size_t off, size_t total) {
+    if (off + 16 <= total) return w;
+    const uint32_t sh = 8 * (uint32_t)(off + 16 - total);  // 8 .. 120
+    uint64_t lo = (uint32_t)w[0] | (uint64_t)(uint32_t)w[1] << 32, hi = (uint32_t)w[2] | (uint64_t)(uint32_t)w[3] << 32;
+    if (sh >= 64) {
+        lo = hi >> (sh - 64);
+        hi = 0;
+    } else {
+        lo = lo >> sh | hi << (64 - sh);
+        hi >>= sh;
+    }
+    return v4i{(int32_t)(uint32_t)lo, (int32_t)(lo >> 32), (int32_t)(uint32_t)hi, (int32_t)(hi >> 32)};
 }
 
 // ---------------------------------------------------------------------------
@@ -234,9 +282,11 @@ __device__ __forceinline__ v4i load_w16(const int8_t* p) {
 // instruction does not affect the sum.
 // ---------------------------------------------------------------------------
 // W operand sources: row-major W read 16 bytes at a time (rows of whole 16-byte
-// granules, 16-byte aligned), row-major W read byte by byte, or W packed in
-// MFMA operand order (see pack_w_kernel).
-enum WLayout { kWRowVec = 0, kWRowScalar = 1, kWPacked = 2 };
+// granules, 16-byte aligned), the same at any width and alignment, or W packed
+// in MFMA operand order (see pack_w_kernel).  Row-major lines are shared by
+// neighbouring k-blocks (64 of a line's 128 bytes each), which at any alignment
+// are not read with the non-temporal hint.
+enum WLayout { kWRowVec = 0, kWRowAny = 1, kWPacked = 2 };
 
 template <int QB, int KW, int KBW, bool VEC, int WL>
 __global__ __launch_bounds__(KW * 64) void server_eval_mfma_small(const int8_t* __restrict__ W, uint32_t m,
@@ -254,7 +304,10 @@ __global__ __launch_bounds__(KW * 64) void server_eval_mfma_small(const int8_t* 
     const uint32_t wrow = row0 + (lane & 15);
     const int kg = lane >> 4;
     const int arow = lane & 15;
-    const int8_t* wbase = W + (size_t)(wrow < m ? wrow : 0) * n;
+    const size_t wrow_off = (size_t)(wrow < m ? wrow : 0) * n;
+    const int8_t* wbase = W + wrow_off;
+    const size_t total = (size_t)m * n;
+    const bool at_end = WL == kWRowAny && (size_t)(row0 + 16) * n + 16 > total;  // (uniform)
 
     // Query elements converted per thread and chunk (four consecutive k each).
     constexpr int NXG = QB * (KC / 4) / (KW * 64);
@@ -283,12 +336,19 @@ __global__ __launch_bounds__(KW * 64) void server_eval_mfma_small(const int8_t* 
                 xq[it][2] = t.z;
                 xq[it][3] = t.w;
             } else {
-                xok[it] = 0u;
+                if (k + 4 <= n) {
+                    const v4u_w t = *reinterpret_cast<const v4u_w*>(xr + k);
+                    xok[it] = okq ? 0xfu : 0u;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const bool ok = okq && k + e < n;
-                    xok[it] |= ok ? (1u << e) : 0u;
-                    xq[it][e] = xr[ok ? k + e : 0];
+                    for (int e = 0; e < 4; ++e) xq[it][e] = t[e];
+                } else {  // the end of the row
+                    xok[it] = 0u;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const bool ok = okq && k + e < n;
+                        xok[it] |= ok ? (1u << e) : 0u;
+                        xq[it][e] = xr[ok ? k + e : 0];
+                    }
                 }
             }
         }
@@ -318,12 +378,7 @@ __global__ __launch_bounds__(KW * 64) void server_eval_mfma_small(const int8_t* 
             if (WL == kWRowVec) {
                 t = load_w16(wbase + (okw ? k : 0u));
             } else {
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const bool ok = okw && k + e < n;
-                    const uint32_t b = (uint32_t)(uint8_t)wbase[ok ? k + e : 0u];
-                    t[e >> 2] |= (int32_t)((ok ? b : 0u) << (8 * (e & 3)));
-                }
+                t = load_w16_any(W, wrow_off + (okw ? k : 0u), total);
             }
             bw[j] = t;
         }
@@ -347,6 +402,10 @@ __global__ __launch_bounds__(KW * 64) void server_eval_mfma_small(const int8_t* 
         for (int j = 0; j < KBW; ++j) {
             const int kbl = wave * KBW + j;
             v4i w;
+            if (WL == kWRowAny && at_end) {
+                const uint32_t k = kc0 + (uint32_t)kbl * 64 + kg * 16;
+                bw[j] = w16_at(bw[j], wrow_off + (wmask[j] ? k : 0u), total);
+            }
             w[0] = bw[j][0] & wmask[j];
             w[1] = bw[j][1] & wmask[j];
             w[2] = bw[j][2] & wmask[j];
@@ -399,7 +458,7 @@ hipError_t launch_mfma_small(const int8_t* W, uint32_t m, uint32_t n, const uint
     } else if (xvec && wvec) {
         MVK_SMALL(true, kWRowVec);
     } else {
-        MVK_SMALL(false, kWRowScalar);
+        MVK_SMALL(false, kWRowAny);
     }
 #undef MVK_SMALL
     return hipGetLastError();
@@ -490,12 +549,7 @@ __global__ __launch_bounds__(256) void digits_tiled_kernel(const uint32_t* __res
             x[4 * v + 3] = ok ? t.w : 0u;
         }
     } else {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const bool ok = okq && k0 + e < n;
-            const uint32_t t = xr[ok ? k0 + e : 0u];
-            x[e] = ok ? t : 0u;
-        }
+        load_x16(x, xr, k0, n, okq);
     }
     int32_t pl[4][4];  // pl[d][w]: digit plane d of elements 4w .. 4w+3
 #pragma unroll
@@ -745,7 +799,7 @@ __global__ __launch_bounds__(NW * 64) void server_eval_mfma_stream(
 // the next chunk's loads issued before the current chunk's MFMAs (two
 // register sets used in turn).  NW waves (eight as launched: four measured
 // no better); rows 16*NW*TWW per workgroup.
-template <int QT, int TWW, int KBM, int C, bool PACKED, int NW>
+template <int QT, int TWW, int KBM, int C, int WL, int NW>
 __global__ __launch_bounds__(NW * 64) void server_eval_mfma_dstat(const int8_t* __restrict__ W, uint32_t m,
                                                                   uint32_t n, const uint32_t* __restrict__ X,
                                                                   uint32_t nkb, uint32_t ksplit, uint32_t B,
@@ -766,12 +820,14 @@ __global__ __launch_bounds__(NW * 64) void server_eval_mfma_dstat(const int8_t* 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t kl = (lane >> 4) * 16;
     const uint32_t nrt = (m + 15) / 16;
-    const int8_t* wptr[TWW];
+    size_t wrow[TWW];  // offset of this lane's row of row tile t (row-major W)
 #pragma unroll
     for (int t = 0; t < TWW; ++t) {
         const uint32_t row = rb * kRows + (wave * TWW + t) * 16 + (lane & 15);
-        wptr[t] = W + (size_t)(row < m ? row : m - 1) * n;
+        wrow[t] = (size_t)(row < m ? row : m - 1) * n;
     }
+    const size_t total = (size_t)m * n;
+    const bool at_end = WL == kWRowAny && (size_t)(rb + 1) * kRows * n + 16 > total;  // (uniform)
     // Each wave walks its k-range from its own starting block (row tile *
     // rot_mul, cyclically): the sum does not depend on the order, and waves
     // of neighbouring row tiles then do not read the same k-offset at once.
@@ -779,15 +835,22 @@ __global__ __launch_bounds__(NW * 64) void server_eval_mfma_dstat(const int8_t* 
     auto rotj = [&](uint32_t j) { return j + rot < nk ? j + rot : j + rot - nk; };  // j < nk
     // B operand of row tile t at local k-block j (in range: blocks past the
     // end re-read the last block of the range, masked out below)
-    auto load_w = [&](uint32_t j, int t) -> v4i {
+    auto kblock = [&](uint32_t j) {
         const uint32_t kbj = kb0 + (j < nk ? rotj(j) : (nk ? rotj(nk - 1) : 0u));
-        const uint32_t kbe = kbj < nkb ? kbj : nkb - 1;
-        if (PACKED) {
+        return kbj < nkb ? kbj : nkb - 1;
+    };
+    auto row_off = [&](uint32_t kbe, int t) {
+        const uint32_t k = kbe * 64 + kl;
+        return wrow[t] + (k < n ? k : 0u);  // columns >= n meet zero digits
+    };
+    auto load_w = [&](uint32_t j, int t) -> v4i {
+        const uint32_t kbe = kblock(j);
+        if (WL == kWPacked) {
             const uint32_t rt = rb * (kRows / 16) + wave * TWW + t;
             return load_w16(W + (((size_t)(rt < nrt ? rt : nrt - 1) * nkb + kbe) * 64 + lane) * 16);
         }
-        const uint32_t k = kbe * 64 + kl;
-        return load_w16(wptr[t] + (k < n ? k : 0u));  // columns >= n meet zero digits
+        if (WL == kWRowVec) return load_w16(W + row_off(kbe, t));
+        return load_w16_any(W, row_off(kbe, t), total);
     };
     // Digit tiles of this k-range into LDS: unit (local k-block, query,
     // 16-element quarter) -> the four granules of digits 0..3 (consecutive lanes
@@ -818,12 +881,7 @@ __global__ __launch_bounds__(NW * 64) void server_eval_mfma_dstat(const int8_t* 
                 x[r][4 * v + 3] = ok ? t.w : 0u;
             }
         } else {
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const bool ok = okq && k0 + e < n;
-                const uint32_t t = xr[ok ? k0 + e : 0u];
-                x[r][e] = ok ? t : 0u;
-            }
+            load_x16(x[r], xr, k0, n, okq);
         }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -867,7 +925,9 @@ __global__ __launch_bounds__(NW * 64) void server_eval_mfma_dstat(const int8_t* 
             for (int i = 0; i < QT; ++i) ca[i] = *reinterpret_cast<const v4i*>(&Dst[jd][i][16 * lane]);
 #pragma unroll
             for (int t = 0; t < TWW; ++t) {
-                const v4i bw = w[c][t] & msk;
+                v4i bw = w[c][t];
+                if (WL == kWRowAny && at_end) bw = w16_at(bw, row_off(kblock(j), t), total);
+                bw &= msk;
 #pragma unroll
                 for (int i = 0; i < QT; ++i)
                     acc[i][t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ca[i], bw, acc[i][t], 0, 0, 0);
@@ -983,12 +1043,7 @@ __global__ __launch_bounds__(256) void digits32_kernel(const uint32_t* __restric
             x[4 * v + 3] = ok ? t.w : 0u;
         }
     } else {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const bool ok = okq && k0 + e < n;
-            const uint32_t t = xr[ok ? k0 + e : 0u];
-            x[e] = ok ? t : 0u;
-        }
+        load_x16(x, xr, k0, n, okq);
     }
     int32_t pl[4][4];  // pl[d][w]: digit plane d of elements 4w .. 4w+3
 #pragma unroll
@@ -1253,7 +1308,7 @@ GroupPlan group_plan(uint32_t m, uint32_t n, uint32_t nb) {
 
 template <int QT, int TWW, int KBM, int C, int NW>
 hipError_t launch_dstat_cfg(const int8_t* W, uint32_t m, uint32_t n, const uint32_t* X, uint32_t nkb, uint32_t B,
-                            const YOut& Y, uint32_t ksplit, unsigned long long* accum, bool packed,
+                            const YOut& Y, uint32_t ksplit, unsigned long long* accum, WLayout wl,
                             hipStream_t s);
 
 // Starting-block step of the digits-stationary kernel's k-walk per row tile
@@ -1267,40 +1322,80 @@ uint32_t dstat_rotation() { return 7u; }
 template <int QT, int TWW, int NW>
 hipError_t launch_dstat_kbm(uint32_t kbm, const int8_t* W, uint32_t m, uint32_t n, const uint32_t* X, uint32_t nkb,
                             uint32_t B, const YOut& Y, uint32_t ksplit, unsigned long long* accum,
-                            bool packed, hipStream_t s) {
+                            WLayout wl, hipStream_t s) {
     constexpr uint32_t kMax = QT == 4 ? kDstatKbm4 : kDstatKbm2;
-    if (kbm == 8) return launch_dstat_cfg<QT, TWW, 8, 8, NW>(W, m, n, X, nkb, B, Y, ksplit, accum, packed, s);
-    if (kbm == 16) return launch_dstat_cfg<QT, TWW, 16, 8, NW>(W, m, n, X, nkb, B, Y, ksplit, accum, packed, s);
-    if (kbm == 32) return launch_dstat_cfg<QT, TWW, 32, 8, NW>(W, m, n, X, nkb, B, Y, ksplit, accum, packed, s);
+    if (kbm == 8) return launch_dstat_cfg<QT, TWW, 8, 8, NW>(W, m, n, X, nkb, B, Y, ksplit, accum, wl, s);
+    if (kbm == 16) return launch_dstat_cfg<QT, TWW, 16, 8, NW>(W, m, n, X, nkb, B, Y, ksplit, accum, wl, s);
+    if (kbm == 32) return launch_dstat_cfg<QT, TWW, 32, 8, NW>(W, m, n, X, nkb, B, Y, ksplit, accum, wl, s);
     if constexpr (kMax >= 64)
         if (kbm == 64)
-            return launch_dstat_cfg<QT, TWW, 64, 8, NW>(W, m, n, X, nkb, B, Y, ksplit, accum, packed, s);
+            return launch_dstat_cfg<QT, TWW, 64, 8, NW>(W, m, n, X, nkb, B, Y, ksplit, accum, wl, s);
     return hipErrorInvalidValue;
 }
 
 template <int QT, int TWW, int KBM, int C, int NW>
 hipError_t launch_dstat_cfg(const int8_t* W, uint32_t m, uint32_t n, const uint32_t* X, uint32_t nkb, uint32_t B,
-                            const YOut& Y, uint32_t ksplit, unsigned long long* accum, bool packed,
+                            const YOut& Y, uint32_t ksplit, unsigned long long* accum, WLayout wl,
                             hipStream_t s) {
     if (ksplit == 0 || ceil_div(nkb, ksplit) > (uint32_t)KBM) return hipErrorInvalidValue;  // LDS holds the range
     if (ksplit > 1 && !accum) return hipErrorInvalidValue;
+    if (wl == kWRowAny && (size_t)m * n < 16) return hipErrorInvalidValue;
     const uint32_t nrb = ceil_div(m, 16 * NW * TWW), per_group = 8 / ksplit;
     const dim3 grid(ceil_div(nrb, per_group) * 8);
     const uint32_t rot = dstat_rotation();
-    if (packed)
-        hipLaunchKernelGGL((server_eval_mfma_dstat<QT, TWW, KBM, C, true, NW>), grid, dim3(NW * 64), 0, s, W, m, n,
-                           X, nkb, ksplit, B, Y, accum, rot);
-    else
-        hipLaunchKernelGGL((server_eval_mfma_dstat<QT, TWW, KBM, C, false, NW>), grid, dim3(NW * 64), 0, s, W, m, n,
-                           X, nkb, ksplit, B, Y, accum, rot);
+#define MVK_DSTAT(WLV)                                                                                            \
+    hipLaunchKernelGGL((server_eval_mfma_dstat<QT, TWW, KBM, C, WLV, NW>), grid, dim3(NW * 64), 0, s, W, m, n, X, \
+                       nkb, ksplit, B, Y, accum, rot)
+    if (wl == kWPacked) MVK_DSTAT(kWPacked);
+    else if (wl == kWRowVec) MVK_DSTAT(kWRowVec);
+    else MVK_DSTAT(kWRowAny);
+#undef MVK_DSTAT
     return hipGetLastError();
+}
+
+hipError_t launch_dstat(const GroupPlan& g, const int8_t* W, uint32_t m, uint32_t n, const uint32_t* X, uint32_t nkb,
+                        uint32_t nb, const YOut& Y, unsigned long long* accum, WLayout wl, hipStream_t s) {
+    if (g.qt == 4)
+        return g.tww == 1 ? launch_dstat_kbm<4, 1, 8>(g.kbm, W, m, n, X, nkb, nb, Y, g.ks, accum, wl, s)
+                          : launch_dstat_kbm<4, 2, 8>(g.kbm, W, m, n, X, nkb, nb, Y, g.ks, accum, wl, s);
+    return g.tww == 1 ? launch_dstat_kbm<2, 1, 8>(g.kbm, W, m, n, X, nkb, nb, Y, g.ks, accum, wl, s)
+                      : launch_dstat_kbm<2, 2, 8>(g.kbm, W, m, n, X, nkb, nb, Y, g.ks, accum, wl, s);
 }
 }  // namespace
 
-ServerEvalPlan server_eval_plan(uint32_t m, uint32_t n, uint32_t B, int path, bool packed) {
+namespace {
+// Queries of the next launch of a row-major product whose rows are not whole
+// aligned 16-byte granules, with `left` queries to go: 16, or 8, on the
+// digits-stationary kernel where the digit tiles of a k-range fit its LDS
+// (n <= 16384 and n <= 32768), else four on the small one.  (The streamed
+// kernels' LDS DMA needs aligned rows.)  Measured on MI355X at 5003 x 3001 with
+// 12 queries: 16.5 us in one launch, against 138.8 us in three launches of
+// four that loaded W byte by byte.
+uint32_t any_group(uint32_t m, uint32_t n, uint32_t left) {
+    for (uint32_t most : {16u, 8u}) {
+        const uint32_t nb = left < most ? left : most;
+        if (nb > 4 && group_plan(m, n, nb).dstat) return nb;
+    }
+    return left < 4 ? left : 4;
+}
+}  // namespace
+
+ServerEvalPlan server_eval_plan(uint32_t m, uint32_t n, uint32_t B, int path, bool packed, bool rows_aligned) {
     ServerEvalPlan pl{0, 0};
-    if (path == MVK_PATH_VALU || B <= 4 || (!packed && n % 16 != 0)) return pl;
+    if (path == MVK_PATH_VALU || B <= 4 || (!packed && (size_t)m * n < 16)) return pl;
     const size_t nkb = ceil_div(n, 64);
+    if (!packed && !rows_aligned) {
+        // the groups repeat every 16 queries: the last 32 at most hold every kind
+        for (uint32_t left = B > 48 ? 32 + B % 16 : B; left;) {
+            const uint32_t nb = any_group(m, n, left);
+            left -= nb;
+            if (nb <= 4) continue;
+            const GroupPlan g = group_plan(m, n, nb);
+            const size_t aw = g.ks > 1 ? (size_t)ceil_div(m, g.rows) * g.rows * g.qt * 4 * 2 : 0;
+            pl.ctrl_words = aw > pl.ctrl_words ? aw : pl.ctrl_words;
+        }
+        return pl;
+    }
     size_t dt_bytes = 0, part_bytes = 0;
     // launch groups hold 64 queries, the last one B % 64 (if nonzero)
     const uint32_t sizes[2] = {B < 64 ? B : 64u, B > 64 ? B % 64 : 0u};
@@ -1342,22 +1437,28 @@ hipError_t launch_server_eval_group(const int8_t* W, uint32_t G, uint32_t mg, ui
         if (B == 2) return launch_cfg<8, 2>(W, m, n, X, B, Y, s);
         return launch_cfg<4, 4>(W, m, n, X, B, Y, s);
     }
+    // (a matrix below 16 bytes: no 16-byte load fits)
+    if (!packed && (size_t)m * n < 16) return launch_cfg<4, 4>(W, m, n, X, B, Y, s);
     if (B == 1) return launch_mfma_small<1, 8, 8>(W, m, n, X, B, out, packed, s);
     if (B == 2) return launch_mfma_small<2, 8, 8>(W, m, n, X, B, out, packed, s);
     if (B <= 4) return launch_mfma_small<4, 8, 4>(W, m, n, X, B, out, packed, s);
+    // the digits-stationary kernel's split-k accumulators share the control
+    // words with the streamed kernel's counters (each launch leaves them zero)
+    unsigned long long* accum = reinterpret_cast<unsigned long long*>(counters);
+    const uint32_t nkb = ceil_div(n, 64);
     if (!packed && (n % 16 != 0 || (uintptr_t)W % 16 != 0)) {
-        // Rows that are not whole 16-byte granules: the streamed path would read
-        // past the end of W on the last row; use the small path per 4 queries.
-        for (uint32_t b0 = 0; b0 < B; b0 += 4) {
-            const uint32_t nb = (B - b0) < 4 ? (B - b0) : 4;
-            const hipError_t e =
-                launch_mfma_small<4, 8, 4>(W, m, n, X + (size_t)b0 * n, nb, yout_shift(out, b0), false, s);
+        for (uint32_t b0 = 0; b0 < B;) {
+            const uint32_t nb = any_group(m, n, B - b0);
+            const uint32_t* Xb = X + (size_t)b0 * n;
+            const YOut Yb = yout_shift(out, b0);
+            const hipError_t e = nb > 4 ? launch_dstat(group_plan(m, n, nb), W, m, n, Xb, nkb, nb, Yb, accum, kWRowAny, s)
+                                        : launch_mfma_small<4, 8, 4>(W, m, n, Xb, nb, Yb, false, s);
             if (e != hipSuccess) return e;
+            b0 += nb;
         }
         return hipSuccess;
     }
     // Up to 64 queries per launch group; W is streamed once per group.
-    const uint32_t nkb = ceil_div(n, 64);
     size_t dt_bytes = 0;
     for (uint32_t b0 = 0; b0 < B; b0 += 64) {
         const GroupPlan g = group_plan(m, n, (B - b0) < 64 ? (B - b0) : 64);
@@ -1367,9 +1468,6 @@ hipError_t launch_server_eval_group(const int8_t* W, uint32_t G, uint32_t mg, ui
         }
     }
     int8_t* Dt = (int8_t*)ws;
-    // the digits-stationary kernel's split-k accumulators share the control
-    // words with the streamed kernel's counters (each launch leaves them zero)
-    unsigned long long* accum = reinterpret_cast<unsigned long long*>(counters);
     uint32_t* part = (uint32_t*)((char*)ws + dt_bytes);
     for (uint32_t b0 = 0; b0 < B; b0 += 64) {
         const uint32_t nb = (B - b0) < 64 ? (B - b0) : 64;
@@ -1378,16 +1476,7 @@ hipError_t launch_server_eval_group(const int8_t* W, uint32_t G, uint32_t mg, ui
         const YOut Yb = yout_shift(out, b0);
         hipError_t e = hipSuccess;
         if (g.dstat) {
-            if (g.qt == 4)
-                e = g.tww == 1 ? launch_dstat_kbm<4, 1, 8>(g.kbm, W, m, n, Xb, nkb, nb, Yb, g.ks, accum,
-                                                           packed, s)
-                               : launch_dstat_kbm<4, 2, 8>(g.kbm, W, m, n, Xb, nkb, nb, Yb, g.ks, accum,
-                                                           packed, s);
-            else
-                e = g.tww == 1 ? launch_dstat_kbm<2, 1, 8>(g.kbm, W, m, n, Xb, nkb, nb, Yb, g.ks, accum,
-                                                           packed, s)
-                               : launch_dstat_kbm<2, 2, 8>(g.kbm, W, m, n, Xb, nkb, nb, Yb, g.ks, accum,
-                                                           packed, s);
+            e = launch_dstat(g, W, m, n, Xb, nkb, nb, Yb, accum, packed ? kWPacked : kWRowVec, s);
             if (e != hipSuccess) return e;
             continue;
         }

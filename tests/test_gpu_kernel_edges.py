@@ -1,0 +1,47 @@
+"""GPU parity at the edges of the kernels' ranges (tile remainders, the smallest
+and largest sizes of a dispatch rule, alignments), against the CPU oracle.
+Every value is an integer mod p: all comparisons are exact."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2609_10264_amd as mvk
+import synth
+from tests.gpu_util import dev, host
+
+pytestmark = pytest.mark.gpu
+
+
+# Row-major W whose rows are not whole aligned 16-byte granules: below 16 bytes
+# in all; one 16-byte load moved down from every row (n < 16); the end of the
+# matrix in a full and in a partial row tile; 4 | 5 queries (small |
+# digits-stationary kernel), 8 | 9 digit tiles, 16 | 17 and more than one group
+# of 16; row lengths around one k-block and around a k split; the longest
+# rows of the digits-stationary kernel (16384) and one more.
+@pytest.mark.parametrize("m,n,B,off", [
+    (1, 7, 3, 1), (3, 5, 6, 0), (2, 8, 5, 3), (5, 3, 9, 2), (16, 1, 5, 0), (129, 17, 4, 0), (128, 63, 5, 0),
+    (127, 65, 8, 5), (257, 127, 9, 0), (130, 1001, 16, 1), (64, 4095, 17, 0), (500, 3001, 12, 0), (33, 4096, 16, 8),
+    (31, 2047, 40, 0), (150, 16383, 16, 0), (20, 16384, 9, 7), (20, 16385, 9, 0), (40, 32767, 8, 0), (17, 33001, 6, 0),
+])
+@pytest.mark.parametrize("p", [synth.P, synth.P_BABYBEAR])
+def test_row_major_any_alignment(m, n, B, off, p):
+    W = synth.weights(500 + m + n, m, n, lo=-128)
+    X = synth.field_uniform(501 + B + n, (B, n), p=p)
+    buf = torch.full((off + m * n + 16,), 0x55, dtype=torch.int8, device="cuda")
+    dW = buf[off:off + m * n].view(m, n)
+    dW.copy_(dev(W))
+    print("row-major", m, n, B, off, p, flush=True)
+    assert np.array_equal(host(mvk.server_eval(dW, dev(X), p=p)), oracle.server_eval(W, X, p=p))
+
+
+# Query rows at any word alignment on packed W (the wide loads of X).
+@pytest.mark.parametrize("m,n,B", [(40, 4099, 1), (200, 1001, 3), (200, 4099, 12), (300, 999, 33), (24600, 130, 20)])
+def test_query_alignment(m, n, B):
+    W = synth.weights(520 + m + n, m, n)
+    X = synth.field_uniform(521 + B + n, (B, n))
+    buf = torch.zeros((B * n + 3,), dtype=torch.int32, device="cuda")
+    for off in (0, 1, 3):
+        dX = buf[off:off + B * n].view(B, n)
+        dX.copy_(dev(X))
+        assert np.array_equal(host(mvk.server_eval(mvk.pack_weights(dev(W)), dX)), oracle.server_eval(W, X))
