@@ -212,8 +212,8 @@ mvk_status mvk_server_eval_packed_static(const int8_t *Wp, uint32_t m, uint32_t 
  *   key : host struct; key->m, key->n, the two codes and the PT, Q buffers
  *         must be set (cx.k == n, cy.k == m)
  *   W   : device, m x n int8
- * Uses a workspace of about m*n + max(Nx*m, Ny*n)*4 bytes (plus 2/256 of that
- * for the segment sums of the prefix scans).
+ * Uses a workspace of about m*n + max(Nx*m, Ny*n)*4 bytes (plus a few percent
+ * for the offsets of the prefix scans' segments).
  * Errors: MVK_EINVAL, MVK_ERANGE (a buffer size above 2^62 bytes, m or n above
  * 65535 * 64), MVK_ENOMEM.
  */

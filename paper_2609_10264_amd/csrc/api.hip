@@ -389,20 +389,47 @@ mvk_status mvk_keygen(const mvk_key* key, const int8_t* W, void* stream) {
     const size_t Nx = (size_t)key->cx.r * n, Ny = (size_t)key->cy.r * m;
     if (too_big(m, n, 1) || too_big(Nx, m, 4) || too_big(Ny, n, 4)) return MVK_ERANGE;
     if (m > kMaxEncVectors || n > kMaxEncVectors) return MVK_ERANGE;
+    // Each of the two encodings: the segmented form where it applies, else the
+    // form with passes for the segment sums; they follow one another in one
+    // scratch region after W^T.
     const size_t wt_bytes = align_up((size_t)m * n);
-    const size_t t3_bytes = align_up((Nx * m > Ny * n ? Nx * m : Ny * n) * sizeof(uint32_t));
-    const size_t seg_words = std::max(encT_seg_words(Nx, m), encT_seg_words(Ny, n));
+    struct {
+        bool seg;
+        size_t bytes, ctrl_words, t3_bytes;
+    } f[2];
+    for (int i = 0; i < 2; ++i) {
+        const mvk_code& c = i ? key->cy : key->cx;
+        const uint32_t nvec = i ? n : m;
+        const bool aligned = c.k % 16 == 0 && (i || (uintptr_t)W % 16 == 0);  // (W^T starts aligned)
+        const size_t N = (size_t)c.k * c.r;
+        f[i].ctrl_words = 0;
+        f[i].t3_bytes = 0;
+        f[i].seg = enc_i8_scratch(c.k, c.r, nvec, aligned, &f[i].bytes, &f[i].ctrl_words);
+        if (!f[i].seg) {
+            f[i].t3_bytes = align_up(N * nvec * sizeof(uint32_t));
+            f[i].bytes = f[i].t3_bytes + encT_seg_words(N, nvec) * sizeof(uint32_t);
+        }
+    }
+    const size_t sc_bytes = std::max(f[0].bytes, f[1].bytes);
     void* ws = nullptr;
-    st = workspace(s, wt_bytes + t3_bytes + seg_words * sizeof(uint32_t), &ws);
+    uint32_t* ctrl = nullptr;
+    st = workspace(s, wt_bytes + sc_bytes, &ws, &ctrl, kCtrlBase + 4 * std::max(f[0].ctrl_words, f[1].ctrl_words));
     if (st) return st;
+    uint32_t* counters = (uint32_t*)((char*)ctrl + kCtrlBase);
     int8_t* WT = (int8_t*)ws;
-    uint32_t* t3 = (uint32_t*)((char*)ws + wt_bytes);
-    uint32_t* seg = (uint32_t*)((char*)ws + wt_bytes + t3_bytes);
-    // P^T = Gx^T W^T: vector i is row i of W = column i of W^T (n positions).
+    char* sc = (char*)ws + wt_bytes;
     hipError_t e = launch_transpose_i8(W, m, n, WT, s);
-    if (e == hipSuccess) e = launch_encT_i8(key->cx, WT, (size_t)m, 1, m, t3, seg, key->PT, (size_t)m, 1, s);
-    // Q = Gy^T W: vector k is column k of W (m positions).
-    if (e == hipSuccess) e = launch_encT_i8(key->cy, W, (size_t)n, 1, n, t3, seg, key->Q, (size_t)n, 1, s);
+    for (int i = 0; i < 2 && e == hipSuccess; ++i) {
+        // P^T = Gx^T W^T: vector v is row v of W = column v of W^T (n positions);
+        // Q = Gy^T W: vector v is column v of W (m positions).
+        const mvk_code& c = i ? key->cy : key->cx;
+        const uint32_t nvec = i ? n : m;
+        const int8_t* in = i ? W : WT;
+        uint32_t* out = i ? key->Q : key->PT;
+        e = f[i].seg ? launch_enc_i8(c, i ? WT : W, in, nvec, sc, f[i].bytes, counters, out, s)
+                     : launch_encT_i8(c, in, (size_t)nvec, 1, nvec, (uint32_t*)sc, (uint32_t*)(sc + f[i].t3_bytes),
+                                      out, (size_t)nvec, 1, s);
+    }
     return hip_status(e);
 }
 

@@ -72,6 +72,53 @@ __device__ __forceinline__ uint32_t fmul(uint32_t a, uint32_t b) {
 
 #endif
 
+// Products with a coefficient that many lanes share (the batched encoding):
+// fcoef is the form in which the coefficient c is kept, fcoef_off that of
+// -128 c, and
+//   fmadd_c(acc, fcoef(c), t)                        = acc + c t          mod p
+//   fmadd_c8(acc, fcoef(c), fcoef_off(c), w + 128)   = acc + c w          mod p
+// for acc, t in [0, p) and an int8 w, given as w + 128 in [0, 255].  A sum of
+// two residues s < 2^32 is brought below p by min(s, s - p) on unsigned words.
+__device__ __forceinline__ uint32_t fmin_p(uint32_t s) { return s < s - kP ? s : s - kP; }
+
+#ifdef MVK_FIELD_BABYBEAR
+// Montgomery form (P. Montgomery, 1985): c 2^32 mod p, and x 2^-32 mod p as
+// (x + m p) / 2^32 with m = -x p^-1 mod 2^32; -p^-1 = 15 * 2^27 - 1 since
+// (15 * 2^27)^2 = 0 mod 2^32.  Below p + x / 2^32.
+__device__ __forceinline__ uint32_t fredc(uint64_t x) {
+    const uint32_t m = (uint32_t)x * (15u * (1u << 27) - 1u);
+    return (uint32_t)((x + (uint64_t)m * kP) >> 32);
+}
+__device__ __forceinline__ uint32_t fcoef(uint32_t c) { return fred64((uint64_t)c << 32); }
+__device__ __forceinline__ uint32_t fcoef_off(uint32_t c) {
+    const uint32_t x = fred64((uint64_t)fcoef(c) << 7);
+    return x ? kP - x : 0u;
+}
+__device__ __forceinline__ uint32_t fmadd_c(uint32_t acc, uint32_t c, uint32_t t) {
+    return fmin_p(acc + fmin_p(fredc((uint64_t)c * t)));  // fredc < 1.5 p
+}
+__device__ __forceinline__ uint32_t fmadd_c8(uint32_t acc, uint32_t c, uint32_t off, uint32_t u) {
+    return fmin_p(acc + fmin_p(fredc((uint64_t)c * u + off)));  // fredc < p + 2^8
+}
+#else
+__device__ __forceinline__ uint32_t fcoef(uint32_t c) { return c; }
+__device__ __forceinline__ uint32_t fcoef_off(uint32_t c) {
+    const uint32_t x = fred64((uint64_t)c << 7);
+    return x ? kP - x : 0u;
+}
+// c t + acc <= (p - 1)^2 + p - 1 = p (p - 1): its two 31-bit halves add up to
+// at most 2 p - 2, so one subtraction of p makes the value canonical.
+__device__ __forceinline__ uint32_t fmadd_c(uint32_t acc, uint32_t c, uint32_t t) {
+    const uint64_t x = (uint64_t)c * t + acc;
+    return fmin_p(((uint32_t)x & kP) + (uint32_t)(x >> 31));
+}
+// c u + off + acc < 2^31 * 255 + 2^32: the upper half is below 2^9
+__device__ __forceinline__ uint32_t fmadd_c8(uint32_t acc, uint32_t c, uint32_t off, uint32_t u) {
+    const uint64_t x = (uint64_t)c * u + (off + acc);
+    return fmin_p(((uint32_t)x & kP) + (uint32_t)(x >> 31));
+}
+#endif
+
 // Signed 64-bit value (|x| < 2^62) -> [0, p).
 __device__ __forceinline__ uint32_t fred_s64(int64_t x) {
     // x + p*2^32 lies in (0, 2^64) for |x| < 2^62 (p*2^32 < 2^63) and is x mod p.

@@ -47,6 +47,14 @@ hipError_t launch_encT_u32(const mvk_code& c, const uint32_t* in, size_t ld_in, 
                            uint32_t* t3, uint32_t* seg, uint32_t* out, size_t ld_out, size_t vs_out, hipStream_t s);
 hipError_t launch_encT_i8(const mvk_code& c, const int8_t* in, size_t ld_in, size_t vs_in, uint32_t nvec,
                           uint32_t* t3, uint32_t* seg, uint32_t* out, size_t ld_out, size_t vs_out, hipStream_t s);
+// G^T of every row of the int8 matrix M (nvec x k, row-major), given as well
+// vectors-innermost (in: k x nvec); element j of vector v goes to
+// out[j * nvec + v].  scratch, counters (zero before the launch, left zero):
+// what enc_i8_scratch says, which is false where the segmented form does not
+// apply (see enc_i8_plan); rows_aligned as server_eval_plan, for M.
+bool enc_i8_scratch(uint32_t k, uint32_t r, uint32_t nvec, bool rows_aligned, size_t* bytes, size_t* ctrl_words);
+hipError_t launch_enc_i8(const mvk_code& c, const int8_t* M, const int8_t* in, uint32_t nvec, void* scratch,
+                         size_t scratch_bytes, uint32_t* counters, uint32_t* out, hipStream_t s);
 // Block lengths above this value run the syndrome in segments of kSynSegLen
 // positions (several workgroups per vector) and need syn_scratch_bytes(count,
 // N) bytes of scratch; up to it the syndrome runs in LDS and needs none.

@@ -20,6 +20,8 @@
 #include "mvk_internal.h"
 #include "syn_block.h"
 
+#include <type_traits>
+
 namespace mvk {
 
 namespace {
@@ -220,6 +222,188 @@ hipError_t launch_encT(const mvk_code& c, const T* in, size_t ld_in, size_t vs_i
         case 4: return launch_enc_r<T, 4>(c, in, ld_in, vs_in, nvec, t3, tot, off, out, ld_out, vs_out, s);
         case 8: return launch_enc_r<T, 8>(c, in, ld_in, vs_in, nvec, t3, tot, off, out, ld_out, vs_out, s);
         default: return launch_enc_r<T, 0>(c, in, ld_in, vs_in, nvec, t3, tot, off, out, ld_out, vs_out, s);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Batched encoding of the rows of an int8 matrix M (nvec x k; Preprocess: W for
+// P^T, W^T for Q) with the segment offsets taken from one server product.
+//
+// The value of either prefix sum just before a segment is a fixed linear map of
+// the vector: with the segments starting at s L,
+//   t3[s L - 1]  = D_s . w,  D_s[i]  = sum of v1[j] over j < s L, pi1[j] / r = i
+//   out[s L - 1] = E_s . w,  E_s     = G e_(sL-1)  (the syndrome of a unit vector)
+// so the offsets of every segment of every vector are the product of M with the
+// 2 (nseg - 1) "queries" D_s, E_s (the matrix-core server product, exact), and
+// neither prefix sum needs a pass that only adds up segments: t3 is written and
+// read once, and the output written once.  (The three-pass form above read W and
+// t3 twice: 1310 us for an 11008 x 4096 keygen at r = 3.)
+// ---------------------------------------------------------------------------
+constexpr uint32_t kSegWaves = 8;   // waves per workgroup
+constexpr uint32_t kSegRows = 8;    // positions per wave and step
+constexpr uint32_t kSegStep = kSegWaves * kSegRows;
+constexpr uint32_t kSegVec = 256;   // vectors per workgroup (four per lane)
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// (loads and stores of four words at any word, of one word at any byte)
+typedef uint32_t u32x4_w __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32_b __attribute__((aligned(1)));
+
+// The code arrays in the form the passes read, padded to whole steps (and one
+// step more, which the passes load ahead) with coefficient 0: row1 = pi1 / r and
+// row2 = pi2 (in range), c1, c1off, c2 as fmadd_c takes them.  Besides, pos =
+// pi1^-1 and the unit vectors e_(sL-1), s = 1 .. nq, of the offsets.
+__global__ __launch_bounds__(256) void enc_prep(uint32_t N, uint32_t npad, uint32_t r, uint32_t L, uint32_t nq,
+                                                const uint32_t* __restrict__ pi1, const uint32_t* __restrict__ pi2,
+                                                const uint32_t* __restrict__ v1, const uint32_t* __restrict__ v2,
+                                                uint32_t* __restrict__ pos, uint32_t* __restrict__ row1,
+                                                uint32_t* __restrict__ row2, uint32_t* __restrict__ c1,
+                                                uint32_t* __restrict__ c1off, uint32_t* __restrict__ c2,
+                                                uint32_t* __restrict__ idx, uint32_t* __restrict__ val) {
+    const uint32_t j = blockIdx.x * 256 + threadIdx.x;
+    if (j < nq) {
+        idx[j] = (j + 1) * L - 1;
+        val[j] = 1u;
+    }
+    if (j >= npad) return;
+    const bool in = j < N;
+    const uint32_t a = in ? pi1[j] : 0u, b = in ? pi2[j] : 0u;
+    const uint32_t p1 = a < N ? a : N - 1;
+    if (in) pos[p1] = j;
+    row1[j] = p1 / r;
+    row2[j] = b < N ? b : N - 1;
+    c1[j] = in ? fcoef(v1[j]) : 0u;
+    c1off[j] = in ? fcoef_off(v1[j]) : 0u;
+    c2[j] = in ? fcoef(v2[j]) : 0u;
+}
+
+// D_s for s = s0+1 .. (grid.y ranges of kDqPer): D[s-1][i], row i per thread.
+constexpr uint32_t kDqPer = 8;
+__global__ __launch_bounds__(256) void enc_dq(uint32_t k, uint32_t r, uint32_t N, uint32_t L, uint32_t nq,
+                                              const uint32_t* __restrict__ pos, const uint32_t* __restrict__ v1,
+                                              uint32_t* __restrict__ D) {
+    const uint32_t i = blockIdx.x * 256 + threadIdx.x, s0 = blockIdx.y * kDqPer;
+    if (i >= k) return;
+    uint64_t acc[kDqPer] = {};
+    for (uint32_t q = 0; q < r; ++q) {
+        uint32_t j = pos[(size_t)i * r + q];
+        if (j >= N) j = N - 1;
+        const uint32_t v = v1[j], sj = j / L;  // position j counts from segment sj + 1 on
+#pragma unroll
+        for (uint32_t e = 0; e < kDqPer; ++e) acc[e] += s0 + e >= sj ? v : 0u;
+    }
+#pragma unroll
+    for (uint32_t e = 0; e < kDqPer; ++e)
+        if (s0 + e < nq) D[(size_t)(s0 + e) * k + i] = fred64(acc[e]);
+}
+
+// One prefix sum of one segment of L positions for the 256 vectors of a tile
+// (four per lane): FIRST: t3 from the int8 rows (in + row * nvec), else the
+// output from t3.  t3 is held tile by tile (N rows of 256 words each).  Each
+// step the waves take kSegRows consecutive positions each, sum them in
+// registers, and add the totals of the waves before them (through LDS) and the
+// segment's running offset.  The code entries (scalar loads of a whole step)
+// are fetched two steps ahead and the rows one step ahead, unconditionally.
+//
+// Bound by HBM: the first sum writes 4 bytes an element and the second reads
+// and writes 4.  At 11008 x 4096, r = 3 (541 MB of t3 and of output): 119 and
+// 215 us, 4.6 and 5.0 TB/s, where a copy of 512 MB runs at 5.4 TB/s; the whole
+// keygen 803 us.  t3 and the output are streamed with the non-temporal hint (950
+// us without it); t3 kept for chunks of 36 to 256 MB of vectors, to stay in the
+// memory-side cache between its write and its read, measured 890 to 1180 us:
+// each launch then has too few workgroups.
+struct SegIdx {
+    uint32_t row[kSegRows];
+};
+template <bool FIRST>
+__global__ __launch_bounds__(kSegWaves * 64, 4) void enc_seg(
+    uint32_t N, uint32_t L, uint32_t nseg, uint32_t ntile, const uint32_t* __restrict__ rows,
+    const uint32_t* __restrict__ coef, const uint32_t* __restrict__ coef_off, const int8_t* __restrict__ in,
+    uint32_t nvec, const uint32_t* __restrict__ off, uint32_t* __restrict__ t3,
+    uint32_t* __restrict__ out) {
+    __shared__ u32x4 tot[2][kSegWaves][64];
+    // (neighbouring workgroups take the tiles of one segment: adjacent output)
+    const uint32_t seg = blockIdx.x / ntile, tile = blockIdx.x - seg * ntile;
+    const int lane = threadIdx.x & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // Lanes past the last vector take the last four, and positions past N
+    // (coefficient 0: their sum is that of position N - 1) are stored to row
+    // N - 1: both write what their neighbours write there, so every store is
+    // unconditional and the waits can count them.
+    const uint32_t vl = (uint32_t)lane * 4;
+    const uint32_t vb = tile * kSegVec + vl + 4 <= nvec ? tile * kSegVec + vl : nvec - 4;
+    t3 += (size_t)tile * N * kSegVec + vl;
+
+    typedef typename std::conditional<FIRST, uint32_t, u32x4>::type Row;
+    auto load_idx = [&](SegIdx& d, uint32_t j) { d = *reinterpret_cast<const SegIdx*>(rows + j); };
+    auto load_rows = [&](Row(&x)[kSegRows], const SegIdx& d) {
+#pragma unroll
+        for (uint32_t e = 0; e < kSegRows; ++e) {
+            if constexpr (FIRST)
+                x[e] = *reinterpret_cast<const u32_b*>(in + (size_t)d.row[e] * nvec + vb);
+            else
+                x[e] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(t3 + (size_t)d.row[e] * kSegVec));
+        }
+    };
+    uint32_t jw = seg * L + wave * kSegRows;  // this wave's positions of the current step
+    SegIdx d;
+    Row cur[kSegRows], nxt[kSegRows];
+    load_idx(d, jw);
+    load_rows(cur, d);
+    load_idx(d, jw + kSegStep);
+    u32x4 carry = {0u, 0u, 0u, 0u};
+    if (seg) carry = *reinterpret_cast<const u32x4_w*>(off + (size_t)(seg - 1) * nvec + vb);
+    auto step = [&](Row(&x)[kSegRows], Row(&y)[kSegRows], int buf) {
+        load_rows(y, d);
+        load_idx(d, jw + 2 * kSegStep);
+        __builtin_amdgcn_sched_barrier(0);  // (the loads stay ahead of the arithmetic)
+        const SegIdx c = *reinterpret_cast<const SegIdx*>(coef + jw);
+        u32x4 a[kSegRows];
+        u32x4 run = {0u, 0u, 0u, 0u};
+        if constexpr (FIRST) {
+            const SegIdx co = *reinterpret_cast<const SegIdx*>(coef_off + jw);
+#pragma unroll
+            for (uint32_t e = 0; e < kSegRows; ++e) {
+                const uint32_t u = x[e] ^ 0x80808080u;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) run[q] = fmadd_c8(run[q], c.row[e], co.row[e], (u >> (8 * q)) & 0xffu);
+                a[e] = run;
+            }
+        } else {
+#pragma unroll
+            for (uint32_t e = 0; e < kSegRows; ++e) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) run[q] = fmadd_c(run[q], c.row[e], x[e][q]);
+                a[e] = run;
+            }
+        }
+        tot[buf][wave][lane] = run;
+        __syncthreads();
+        u32x4 before = carry;
+#pragma unroll
+        for (uint32_t w = 0; w < kSegWaves; ++w) {
+            const u32x4 t = tot[buf][w][lane];
+            if (w == wave) before = carry;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) carry[q] = fmin_p(carry[q] + t[q]);
+        }
+#pragma unroll
+        for (uint32_t e = 0; e < kSegRows; ++e) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) a[e][q] = fmin_p(a[e][q] + before[q]);
+            const uint32_t j = jw + e < N ? jw + e : N - 1;
+            if constexpr (FIRST)
+                __builtin_nontemporal_store(a[e], reinterpret_cast<u32x4*>(t3 + (size_t)j * kSegVec));
+            else
+                __builtin_nontemporal_store((u32x4_w)a[e], reinterpret_cast<u32x4_w*>(out + (size_t)j * nvec + vb));
+        }
+        jw += kSegStep;
+    };
+    // two register sets in turn; segments are an even number of steps, so that
+    // no step's loads are conditional
+    for (uint32_t t = 0; t < L / kSegStep; t += 2) {
+        step(cur, nxt, 0);
+        step(nxt, cur, 1);
     }
 }
 
@@ -536,19 +720,53 @@ hipError_t launch_syn(const mvk_code& c, const uint32_t* v, const uint32_t* idx,
     return launch_seg_sets<SPARSE>(a, s);
 }
 
+// W (m x n) -> WT (n x m) in tiles of T x T: a thread takes 4 x 4 blocks (one
+// word from each of four rows, transposed in registers), so both sides move
+// words, T consecutive bytes per row of a tile; what is left at the edges goes
+// byte by byte.  T is 128, or 64 where tiles of 128 do not fill the chip.  (11008
+// x 4096: 16 us, against 65 with byte loads and stores.)
+template <uint32_t T>
 __global__ __launch_bounds__(256) void transpose_i8(const int8_t* __restrict__ W, uint32_t m, uint32_t n,
                                                     int8_t* __restrict__ WT) {
-    __shared__ int8_t tile[64][65];
-    const uint32_t r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    for (int i = ty; i < 64; i += 4) {
-        const uint32_t r = r0 + i, c = c0 + tx;
-        tile[i][tx] = (r < m && c < n) ? W[(size_t)r * n + c] : (int8_t)0;
+    __shared__ uint32_t tile[T][T / 4 + 1];  // [column][group of four rows]
+    const uint32_t r0 = blockIdx.y * T, c0 = blockIdx.x * T;
+    const bool whole = r0 + T <= m && c0 + T <= n;  // (uniform)
+#pragma unroll
+    for (uint32_t b = 0; b < T * T / 4096; ++b) {
+        const uint32_t cg = threadIdx.x % (T / 4), rg = threadIdx.x / (T / 4) + 1024 / T * b;  // groups of four columns, rows
+        uint32_t w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t row = r0 + 4 * rg + i, col = c0 + 4 * cg;
+            if (whole || (row < m && col + 4 <= n)) {
+                w[i] = *reinterpret_cast<const u32_b*>(W + (size_t)row * n + col);
+            } else {
+                w[i] = 0;
+                for (uint32_t e = 0; e < 4; ++e)
+                    if (row < m && col + e < n) w[i] |= (uint32_t)(uint8_t)W[(size_t)row * n + col + e] << (8 * e);
+            }
+        }
+        // v_perm_b32(S0, S1, sel): selector bytes 0..3 pick bytes of S1, 4..7 of S0
+        const uint32_t a0 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u);  // w0.0 w1.0 w0.1 w1.1
+        const uint32_t a1 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u);  // w0.2 w1.2 w0.3 w1.3
+        const uint32_t b0 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
+        const uint32_t b1 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
+        tile[4 * cg + 0][rg] = __builtin_amdgcn_perm(b0, a0, 0x05040100u);
+        tile[4 * cg + 1][rg] = __builtin_amdgcn_perm(b0, a0, 0x07060302u);
+        tile[4 * cg + 2][rg] = __builtin_amdgcn_perm(b1, a1, 0x05040100u);
+        tile[4 * cg + 3][rg] = __builtin_amdgcn_perm(b1, a1, 0x07060302u);
     }
     __syncthreads();
-    for (int i = ty; i < 64; i += 4) {
-        const uint32_t c = c0 + i, r = r0 + tx;  // WT[c][r] = W[r][c]
-        if (c < n && r < m) WT[(size_t)c * m + r] = tile[tx][i];
+#pragma unroll
+    for (uint32_t b = 0; b < T * T / 1024; ++b) {
+        const uint32_t rg = threadIdx.x % (T / 4), c = threadIdx.x / (T / 4) + 1024 / T * b;
+        const uint32_t w = tile[c][rg], col = c0 + c, row = r0 + 4 * rg;
+        if (whole || (col < n && row + 4 <= m)) {
+            *reinterpret_cast<u32_b*>(WT + (size_t)col * m + row) = w;
+        } else if (col < n) {
+            for (uint32_t e = 0; e < 4; ++e)
+                if (row + e < m) WT[(size_t)col * m + row + e] = (int8_t)(w >> (8 * e));
+        }
     }
 }
 
@@ -562,6 +780,94 @@ __global__ void fill_u32(uint32_t* p, size_t count, uint32_t value) {
 size_t encT_seg_words(size_t N, size_t nvec) {
     const size_t L = enc_seg_len(N, nvec);
     return 2 * ((N + L - 1) / L) * nvec;
+}
+
+// Plan of the segmented encoding of an int8 matrix: 32 segments (62 queries, one
+// launch of the server product; 64 segments measured 10% longer at 11008 x
+// 4096).  It pays where t3 no longer fits the memory-side cache: 2048 x 2048, r
+// = 3 (t3 of 50 MB) takes 174 us against 152 on the three-pass form, 4096 x
+// 4096 (201 MB) 341 to 380 against 416 to 431; with M's rows not whole aligned
+// granules the product takes four launches (4095 x 4097: 561 us against 517).
+// Fewer vectors than 2048 make too few workgroups (11008 x 256: 306 us against
+// 178 with 128 segments).
+namespace {
+constexpr uint32_t kEncSegs = 32;
+constexpr size_t kEncSegsAbove = (size_t)192 << 20, kEncSegsAboveAny = (size_t)400 << 20;  // bytes of t3
+struct EncPlan {
+    uint32_t nseg, L, nq, ntile, npad;  // npad: positions the passes read (whole segments, two more steps)
+    size_t o_pos, o_row1, o_row2, o_c1, o_c1off, o_c2, o_idx, o_val, o_qry, o_off, o_syn, o_srv, o_t3, bytes;
+    ServerEvalPlan srv;
+};
+bool enc_i8_plan(uint32_t k, uint32_t r, uint32_t nvec, bool rows_aligned, EncPlan* out) {
+    const size_t N = (size_t)k * r, unit = 2 * kSegStep;  // (an even number of steps per segment)
+    if (k > MVK_MAX_N || nvec < 2048 || N < kEncSegs * unit) return false;
+    if (4 * N * nvec < (rows_aligned ? kEncSegsAbove : kEncSegsAboveAny)) return false;
+    EncPlan p{};
+    p.ntile = ceil_div(nvec, kSegVec);
+    p.L = (uint32_t)((N + kEncSegs * unit - 1) / (kEncSegs * unit) * unit);
+    p.nseg = (uint32_t)((N + p.L - 1) / p.L);
+    p.nq = p.nseg - 1;
+    p.srv = server_eval_plan(nvec, k, 2 * p.nq, MVK_PATH_AUTO, false, rows_aligned);
+    size_t b = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = b;
+        b += (bytes + 255) & ~(size_t)255;
+        return at;
+    };
+    p.o_pos = take(4 * N);
+    p.npad = p.nseg * p.L + 2 * kSegStep;
+    p.o_row1 = take(4 * (size_t)p.npad);
+    p.o_row2 = take(4 * (size_t)p.npad);
+    p.o_c1 = take(4 * (size_t)p.npad);
+    p.o_c1off = take(4 * (size_t)p.npad);
+    p.o_c2 = take(4 * (size_t)p.npad);
+    p.o_idx = take(4 * (size_t)p.nq);
+    p.o_val = take(4 * (size_t)p.nq);
+    p.o_qry = take(4 * (size_t)2 * p.nq * k);
+    p.o_off = take(4 * (size_t)2 * p.nq * nvec);
+    p.o_syn = take(syn_scratch_bytes(p.nq, N));
+    p.o_srv = take(p.srv.ws_bytes);
+    p.o_t3 = take(4 * N * kSegVec * p.ntile);
+    p.bytes = b;
+    *out = p;
+    return true;
+}
+
+}  // namespace
+
+bool enc_i8_scratch(uint32_t k, uint32_t r, uint32_t nvec, bool rows_aligned, size_t* bytes, size_t* ctrl_words) {
+    EncPlan p;
+    if (!enc_i8_plan(k, r, nvec, rows_aligned, &p)) return false;
+    *bytes = p.bytes;
+    *ctrl_words = p.srv.ctrl_words;
+    return true;
+}
+
+hipError_t launch_enc_i8(const mvk_code& c, const int8_t* M, const int8_t* in, uint32_t nvec, void* scratch,
+                         size_t scratch_bytes, uint32_t* counters, uint32_t* out, hipStream_t s) {
+    EncPlan p;
+    if (!enc_i8_plan(c.k, c.r, nvec, c.k % 16 == 0 && (uintptr_t)M % 16 == 0, &p) || p.bytes > scratch_bytes)
+        return hipErrorInvalidValue;
+    const uint32_t N = c.k * c.r;
+    char* ws = reinterpret_cast<char*>(scratch);
+    auto at = [&](size_t o) { return reinterpret_cast<uint32_t*>(ws + o); };
+    hipLaunchKernelGGL(enc_prep, dim3(ceil_div(p.npad, 256)), dim3(256), 0, s, N, p.npad, c.r, p.L, p.nq, c.pi1,
+                       c.pi2, c.v1, c.v2, at(p.o_pos), at(p.o_row1), at(p.o_row2), at(p.o_c1), at(p.o_c1off),
+                       at(p.o_c2), at(p.o_idx), at(p.o_val));
+    hipLaunchKernelGGL(enc_dq, dim3(ceil_div(c.k, 256), ceil_div(p.nq, kDqPer)), dim3(256), 0, s, c.k, c.r, N, p.L,
+                       p.nq, at(p.o_pos), c.v1, at(p.o_qry));
+    hipError_t e = launch_syn_sparse(c, at(p.o_idx), at(p.o_val), 1, p.nq, nullptr, at(p.o_syn),
+                                     at(p.o_qry) + (size_t)p.nq * c.k, s);
+    if (e != hipSuccess) return e;
+    e = launch_server_eval(M, nvec, c.k, at(p.o_qry), 2 * p.nq, at(p.o_off), MVK_PATH_AUTO, false, ws + p.o_srv,
+                           counters, s);
+    if (e != hipSuccess) return e;
+    const dim3 grid(p.ntile * p.nseg), block(kSegWaves * 64);
+    hipLaunchKernelGGL(enc_seg<true>, grid, block, 0, s, N, p.L, p.nseg, p.ntile, at(p.o_row1), at(p.o_c1),
+                       at(p.o_c1off), in, nvec, at(p.o_off), at(p.o_t3), nullptr);
+    hipLaunchKernelGGL(enc_seg<false>, grid, block, 0, s, N, p.L, p.nseg, p.ntile, at(p.o_row2), at(p.o_c2), nullptr,
+                       nullptr, nvec, at(p.o_off) + (size_t)p.nq * nvec, at(p.o_t3), out);
+    return hipGetLastError();
 }
 
 hipError_t launch_encT_u32(const mvk_code& c, const uint32_t* in, size_t ld_in, size_t vs_in, uint32_t nvec,
@@ -613,7 +919,10 @@ hipError_t launch_syn_sparse(const mvk_code& c, const uint32_t* idx, const uint3
 
 hipError_t launch_transpose_i8(const int8_t* W, uint32_t m, uint32_t n, int8_t* WT, hipStream_t s) {
     if (m == 0 || n == 0) return hipSuccess;
-    hipLaunchKernelGGL(transpose_i8, dim3(ceil_div(n, 64), ceil_div(m, 64)), dim3(256), 0, s, W, m, n, WT);
+    if ((uint64_t)ceil_div(n, 128) * ceil_div(m, 128) >= 256)
+        hipLaunchKernelGGL(transpose_i8<128>, dim3(ceil_div(n, 128), ceil_div(m, 128)), dim3(256), 0, s, W, m, n, WT);
+    else
+        hipLaunchKernelGGL(transpose_i8<64>, dim3(ceil_div(n, 64), ceil_div(m, 64)), dim3(256), 0, s, W, m, n, WT);
     return hipGetLastError();
 }
 

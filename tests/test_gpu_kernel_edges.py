@@ -45,3 +45,21 @@ def test_query_alignment(m, n, B):
         dX = buf[off:off + B * n].view(B, n)
         dX.copy_(dev(X))
         assert np.array_equal(host(mvk.server_eval(mvk.pack_weights(dev(W)), dX)), oracle.server_eval(W, X))
+
+
+# keygen with the segment offsets from one server product (at least 2048 vectors
+# and 192 MB of intermediate sums, 400 MB where the matrix rows are not whole
+# 16-byte granules): the fewest vectors, both encodings; an odd number of
+# vectors (the last lane takes the last four) with a ragged last segment, next
+# to Q on the three-pass form; odd row lengths on both sides; one vector too few.
+@pytest.mark.parametrize("m,n,rx,ry", [(2048, 8192, 3, 3), (2051, 6400, 4, 4), (2049, 16387, 4, 3), (2047, 8192, 3, 2)])
+@pytest.mark.parametrize("p", [synth.P, synth.P_BABYBEAR])
+def test_keygen_segments(m, n, rx, ry, p):
+    from tests.gpu_util import code
+    print("keygen", m, n, rx, ry, p, flush=True)
+    W = synth.weights(540 + m + n, m, n, lo=-128)
+    cx, cy = synth.raa_code(541 + n, n, rx, p=p), synth.raa_code(542 + m, m, ry, p=p)
+    key = mvk.keygen(mvk.Key.allocate(m, n, code(cx, p), code(cy, p)), dev(W))
+    PT, Q = oracle.keygen(W, cx, cy, p=p, nthreads=oracle.threads())
+    assert np.array_equal(host(key.PT), PT)
+    assert np.array_equal(host(key.Q), Q)
