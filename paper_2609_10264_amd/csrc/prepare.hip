@@ -520,7 +520,7 @@ PrepPlan plan_with_cols(PrepPlan pl, const PrepInputDesc* ins, uint32_t NI, cons
     pl.wide = cols == kWideCols;
     if (pl.split && pl.vec && !pl.wide) {
         const PrepPlan w = plan_with_cols(pl, ins, NI, probs, G, kWideCols);
-        if (w.grid >= 256) return w;
+        if (w.split && w.grid >= 256) return w;  // (the wide items exist in the split form only)
     }
     return pl;
 }

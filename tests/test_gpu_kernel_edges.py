@@ -63,3 +63,26 @@ def test_keygen_segments(m, n, rx, ry, p):
     PT, Q = oracle.keygen(W, cx, cy, p=p, nthreads=oracle.threads())
     assert np.array_equal(host(key.PT), PT)
     assert np.array_equal(host(key.Q), Q)
+
+
+# Preparations whose gathers take their own launch: many columns of a short
+# matrix, where items of 1024 columns would no longer need that launch; short
+# syndromes that join long ones (up to 256 of them, and one more); batch
+# verification with one long and one short code.
+@pytest.mark.parametrize("m,n,rx,ry,B,tx", [(1024, 64, 2, 2, 300, 8), (8192, 300, 3, 3, 40, 20), (4352, 6000, 3, 2, 62, 70),
+                                            (16400, 64, 2, 2, 254, 8), (16400, 64, 2, 2, 260, 8)])
+@pytest.mark.parametrize("p", [synth.P, synth.P_BABYBEAR])
+def test_prepare_split(m, n, rx, ry, B, tx, p):
+    from tests.gpu_util import Instance
+    print("prepare", m, n, rx, ry, B, tx, p, flush=True)
+    t = Instance(600 + m + B, m, n, B, rx, tx, 31, 2, ry=ry, p=p)
+    t.to_device()
+    mvk.keygen(t.key, t.dW)
+    prep = mvk.client_prepare(t.key, t.dexi, t.dexv, t.deyi, t.deyv)
+    zero = np.zeros((B, n), dtype=np.uint32)
+    Mx = oracle.encode(t.cx, zero, t.exi, t.exv, p=p)
+    assert np.array_equal(host(prep.Mx), Mx)
+    assert np.array_equal(host(prep.My), oracle.server_eval(t.W, Mx, p=p))
+    R = oracle.encode(t.cy, np.zeros((2, m), dtype=np.uint32), t.eyi, t.eyv, p=p)
+    assert np.array_equal(host(prep.R), R)
+    assert np.array_equal(host(prep.U), oracle.server_eval(np.ascontiguousarray(t.W.T), R, p=p))
