@@ -19,6 +19,7 @@
 #include "field.h"
 #include "mvk_internal.h"
 #include "syn_block.h"
+#include "syn_seg.h"
 
 #include <type_traits>
 
@@ -414,7 +415,7 @@ __global__ __launch_bounds__(kSegWaves * 64, 4) void enc_seg(
 constexpr int kSynThreads = 1024;
 constexpr int kSynMaxU = 16;
 static_assert((size_t)kSynThreads * kSynMaxU == kSynScratchAbove, "LDS syndrome covers the scratch-free range");
-using syn::wave_incl_scan_dpp;
+using namespace synseg;
 
 template <bool SPARSE, int U>
 __global__ __launch_bounds__(kSynThreads) void syn_wg(uint32_t k, uint32_t r, const uint32_t* __restrict__ pi1,
@@ -448,75 +449,37 @@ __global__ __launch_bounds__(kSynThreads) void syn_wg(uint32_t k, uint32_t r, co
 // look-back state: per vector one ticket word and one status word per segment
 // (bit 32 set once the segment's sum, in the low 31 bits, is published).
 // ---------------------------------------------------------------------------
-constexpr int kSegThreads = 256;
-constexpr int kSegPer = 4;
-constexpr uint32_t kSegLen = kSegThreads * kSegPer;
-static_assert(kSegLen == kSynSegLen, "segment length of the scratch layout");
-// Bound on the polls of one look-back read (each followed by a short sleep):
-// every awaited segment belongs to a workgroup that is already running, so the
-// bound is only a guard that makes every wave exit.
-constexpr uint32_t kLookSpinLimit = 1u << 22;
-
-__device__ __forceinline__ unsigned long long* look_state(uint32_t* scratch, uint32_t count, uint32_t N, uint32_t c) {
-    const uint32_t nseg = (N + kSegLen - 1) / kSegLen;
-    return reinterpret_cast<unsigned long long*>(scratch + (size_t)count * 2 * N) + (size_t)c * (nseg + 1);
-}
-
-__device__ __forceinline__ uint64_t block_sum_u64_256(uint64_t v, uint64_t* red) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int s = 32; s >= 1; s >>= 1) {
-        const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, s);
-        const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), s);
-        v += ((uint64_t)hi << 32) | lo;
-    }
-    if (lane == 0) red[wave] = v;
-    __syncthreads();
-    const uint64_t t = red[0] + red[1] + red[2] + red[3];
-    __syncthreads();
-    return t;
-}
-
-// Inclusive suffix scan of the kSegPer consecutive values x[] owned by each of
-// the 256 threads (thread t owns positions t*kSegPer ..), plus `carry`.
-__device__ __forceinline__ void seg_suffix_scan(uint32_t (&x)[kSegPer], uint32_t carry, uint32_t* wsum) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int e = kSegPer - 2; e >= 0; --e) x[e] = fadd(x[e], x[e + 1]);
-    const uint32_t incl = wave_incl_scan_dpp(x[0]);  // prefix over lanes of thread totals
-    if (lane == 63) wsum[wave] = incl;
-    __syncthreads();
-    const uint32_t w0 = wsum[0], w1 = wsum[1], w2 = wsum[2], w3 = wsum[3];
-    __syncthreads();
-    const uint32_t total = fadd(fadd(w0, w1), fadd(w2, w3));
-    uint32_t before = 0;  // totals of earlier waves
-    if (wave > 0) before = w0;
-    if (wave > 1) before = fadd(before, w1);
-    if (wave > 2) before = fadd(before, w2);
-    // sum over later threads = total - (prefix through this thread)
-    const uint32_t after = fsub(total, fadd(before, incl));
-    const uint32_t off = fadd(after, carry);
-#pragma unroll
-    for (int e = 0; e < kSegPer; ++e) x[e] = fadd(x[e], off);
-}
-
 // Several syndromes of long blocks share each of the three launches: set i is
 // count vectors over its own code, with its own work region (count x 2N words
 // and the look-back state).  grid.y runs over the vectors of all sets, grid.x
 // over the segments (p1, p2) or the fold chunks (p3) of the longest; the
 // workgroups past a shorter set's end return at once (before p2's ticket).
-struct SegSet {
-    const uint32_t *pi1, *pi2, *v1, *v2;
-    const uint32_t *vin, *idx, *val, *X;
-    uint32_t* out;
-    uint32_t* work;
-    uint32_t k, r, t, count;
-};
 struct SegArgs {
     uint32_t S;
+    uint32_t by_xcd;             // vectors [0, by_xcd) are placed by XCD (seg_place)
     uint32_t vend[kMaxSynSets];  // vectors of sets < i + 1
     SegSet set[kMaxSynSets];
 };
+
+// Which vector and segment a workgroup of the (segments, vectors) grid takes.
+// Workgroups go to the 8 XCDs in turn by their linear index, and each XCD has
+// its own L2.  The scatters write 4-byte words all over a vector's work array:
+// with a vector's segments on every XCD each L2 held a few words of every line,
+// and the lines went to memory in pieces.  Vectors below by_xcd (a multiple of
+// 8) are taken eight at a time, one per XCD, so that one L2 collects whole
+// lines; the vectors left over keep the plain order, which spreads each over
+// the chip.
+constexpr uint32_t kXcds = 8;
+__device__ __forceinline__ void seg_place(const SegArgs& a, uint32_t* vy, uint32_t* seg) {
+    if (blockIdx.y >= a.by_xcd) {
+        *vy = blockIdx.y;
+        *seg = blockIdx.x;
+        return;
+    }
+    const uint32_t within = blockIdx.x + gridDim.x * (blockIdx.y % kXcds);  // of eight vectors' workgroups
+    *vy = blockIdx.y - blockIdx.y % kXcds + within % kXcds;
+    *seg = within / kXcds;
+}
 
 // The set of global vector vy (grid.y) and the vector's index within it.
 __device__ __forceinline__ const SegSet& seg_set(const SegArgs& a, uint32_t vy, uint32_t* c) {
@@ -526,142 +489,46 @@ __device__ __forceinline__ const SegSet& seg_set(const SegArgs& a, uint32_t vy, 
     return a.set[i];
 }
 
-template <bool SPARSE>
+template <bool SPARSE, int NS>
 __global__ __launch_bounds__(kSegThreads) void syn_p1(const SegArgs a) {
-    __shared__ uint32_t seg[kSegLen];
-    __shared__ uint64_t red[4];
-    __shared__ uint32_t wsum[4];
-    uint32_t c;
-    const SegSet& S = seg_set(a, blockIdx.y, &c);
-    const uint32_t N = S.k * S.r, nseg = (N + kSegLen - 1) / kSegLen;
-    if (blockIdx.x >= nseg) return;
-    const uint32_t j0 = blockIdx.x * kSegLen, j1 = (j0 + kSegLen < N) ? j0 + kSegLen : N;
-    const int tid = threadIdx.x;
-    const uint32_t t = S.t;
-    const uint32_t* __restrict__ idx = S.idx;
-    const uint32_t* __restrict__ val = S.val;
-    uint32_t* bbuf = S.work + (size_t)c * 2 * N;
-    if (tid == 0) {
-        // p2's look-back state: this segment's status word, and (segment 0) the ticket
-        unsigned long long* st = look_state(S.work, S.count, N, c);
-        st[1 + blockIdx.x] = 0ull;
-        if (blockIdx.x == 0) st[0] = 0ull;
-    }
-    // code entries of this thread's positions (in flight during the carry)
-    uint32_t p2[kSegPer], w2[kSegPer];
-#pragma unroll
-    for (int e = 0; e < kSegPer; ++e) {
-        const uint32_t j = j0 + tid * kSegPer + e;
-        const uint32_t js = j < j1 ? j : j0;
-        p2[e] = S.pi2[js];
-        w2[e] = S.v2[js];
-    }
-    uint64_t part = 0;
-    if (SPARSE) {
-        for (uint32_t q = tid; q < t; q += kSegThreads) {
-            const uint32_t j = idx[(size_t)c * t + q];
-            if (j >= j1 && j < N) part += val[(size_t)c * t + q];
-        }
-    } else {
-        const uint32_t* src = S.vin + (size_t)c * N;
-        for (uint32_t j = j1 + tid; j < N; j += kSegThreads) part += src[j];
-    }
-    const uint32_t carry = fred64(block_sum_u64_256(part, red));
-    uint32_t x[kSegPer];
-    if (SPARSE) {
-#pragma unroll
-        for (int e = 0; e < kSegPer; ++e) seg[tid * kSegPer + e] = 0u;
-        __syncthreads();
-        for (uint32_t q = tid; q < t; q += kSegThreads) {
-            const uint32_t j = idx[(size_t)c * t + q];
-            if (j >= j0 && j < j1) seg[j - j0] = val[(size_t)c * t + q];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int e = 0; e < kSegPer; ++e) x[e] = seg[tid * kSegPer + e];
-    } else {
-#pragma unroll
-        for (int e = 0; e < kSegPer; ++e) {
-            const uint32_t j = j0 + tid * kSegPer + e;
-            x[e] = j < j1 ? S.vin[(size_t)c * N + j] : 0u;
-        }
-    }
-    seg_suffix_scan(x, carry, wsum);  // A
-#pragma unroll
-    for (int e = 0; e < kSegPer; ++e) {
-        const uint32_t j = j0 + tid * kSegPer + e;
-        if (j < j1) bbuf[p2[e] < N ? p2[e] : N - 1] = fmul(w2[e], x[e]);  // V2, then Pi2 scatter
-    }
+    __shared__ SegLds<NS> lds;
+    uint32_t c, vy, sg;
+    seg_place(a, &vy, &sg);
+    if (vy >= a.vend[a.S - 1]) return;
+    const SegSet& S = seg_set(a, vy, &c);
+    if (sg >= seg_count<NS>(S.k * S.r)) return;
+    seg_first<SPARSE, NS>(S, c, sg, lds);
 }
 
+template <int NS>
 __global__ __launch_bounds__(kSegThreads) void syn_p2(const SegArgs a) {
-    __shared__ uint64_t red[4];
-    __shared__ uint32_t wsum[4];
-    __shared__ uint32_t sh_seg, sh_carry;
-    uint32_t c;
-    const SegSet& S = seg_set(a, blockIdx.y, &c);
-    const uint32_t N = S.k * S.r, nseg = (N + kSegLen - 1) / kSegLen;
-    if (blockIdx.x >= nseg) return;  // (uniform: no ticket taken)
-    const int tid = threadIdx.x, lane = tid & 63;
-    unsigned long long* st = look_state(S.work, S.count, N, c);
-    if (tid == 0) {
-        const uint32_t ticket = atomicAdd(reinterpret_cast<uint32_t*>(st), 1u);  // < nseg: one per workgroup
-        sh_seg = ticket < nseg ? nseg - 1 - ticket : 0u;
-    }
-    __syncthreads();
-    const uint32_t sg = sh_seg;
-    const uint32_t j0 = sg * kSegLen, j1 = (j0 + kSegLen < N) ? j0 + kSegLen : N;
-    const uint32_t* bbuf = S.work + (size_t)c * 2 * N;
+    __shared__ SegLds<NS> lds;
+    uint32_t c, vy, place;
+    seg_place(a, &vy, &place);
+    if (vy >= a.vend[a.S - 1]) return;
+    const SegSet& S = seg_set(a, vy, &c);
+    const uint32_t N = S.k * S.r;
+    if (place >= seg_count<NS>(N)) return;  // (uniform: no ticket taken)
+    uint32_t x[NS][kSegPer], p1[NS][kSegPer], w1[NS][kSegPer];
+    const uint32_t sg = seg_second_load<NS>(S, c, lds, x, p1, w1);
+    seg_second_scan<NS>(S, c, sg, lds, x);
+    const uint32_t j0 = sg * NS * kSegLen + threadIdx.x * kSegPer;
     uint32_t* dbuf = S.work + (size_t)c * 2 * N + N;
-    uint32_t p1[kSegPer], w1[kSegPer], x[kSegPer];
 #pragma unroll
-    for (int e = 0; e < kSegPer; ++e) {
-        const uint32_t j = j0 + tid * kSegPer + e;
-        const uint32_t js = j < j1 ? j : j0;
-        p1[e] = S.pi1[js];
-        w1[e] = S.v1[js];
-        const uint32_t b = bbuf[js];
-        x[e] = j < j1 ? b : 0u;
-    }
-    // publish this segment's sum
-    const uint32_t own = fred64(block_sum_u64_256((uint64_t)x[0] + x[1] + x[2] + x[3], red));
-    if (tid == 0) __hip_atomic_store(&st[1 + sg], (1ull << 32) | own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // carry = sum of the later segments' sums, read 64 segments at a time
-    if (tid < 64) {
-        uint64_t acc = 0;
-        for (uint32_t base = sg + 1; base < nseg; base += 64) {
-            const uint32_t q = base + lane;
-            if (q < nseg) {
-                unsigned long long v = __hip_atomic_load(&st[1 + q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                for (uint32_t spin = 0; !(v >> 32) && spin < kLookSpinLimit; ++spin) {
-                    __builtin_amdgcn_s_sleep(1);
-                    v = __hip_atomic_load(&st[1 + q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
-                acc += (uint32_t)v;
-            }
-        }
+    for (int v = 0; v < NS; ++v)
 #pragma unroll
-        for (int sh = 32; sh >= 1; sh >>= 1) {
-            const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)acc, sh);
-            const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(acc >> 32), sh);
-            acc += ((uint64_t)hi << 32) | lo;
-        }
-        if (tid == 0) sh_carry = fred64(acc);
-    }
-    __syncthreads();
-    seg_suffix_scan(x, sh_carry, wsum);  // A
-#pragma unroll
-    for (int e = 0; e < kSegPer; ++e) {
-        const uint32_t j = j0 + tid * kSegPer + e;
-        if (j < j1) dbuf[p1[e] < N ? p1[e] : N - 1] = fmul(w1[e], x[e]);  // V1, then Pi1 scatter
-    }
+        for (int e = 0; e < kSegPer; ++e)
+            if (j0 + v * kSegLen + e < N)
+                dbuf[p1[v][e] < N ? p1[v][e] : N - 1] = fmul(w1[v][e], x[v][e]);  // V1, then Pi1 scatter
 }
 
 __global__ __launch_bounds__(256) void syn_p3(const SegArgs a) {
-    uint32_t c;
-    const SegSet& S = seg_set(a, blockIdx.y, &c);
+    uint32_t c, vy, chunk;
+    seg_place(a, &vy, &chunk);
+    if (vy >= a.vend[a.S - 1]) return;
+    const SegSet& S = seg_set(a, vy, &c);
     const uint32_t N = S.k * S.r;
-    const uint32_t i = blockIdx.x * 256 + threadIdx.x;
+    const uint32_t i = chunk * 256 + threadIdx.x;
     if (i >= S.k) return;
     const uint32_t* dbuf = S.work + (size_t)c * 2 * N + N;
     uint32_t s = 0;
@@ -672,25 +539,39 @@ __global__ __launch_bounds__(256) void syn_p3(const SegArgs a) {
 
 // The three launches over sets of one input kind (sparse or dense).
 template <bool SPARSE>
-hipError_t launch_seg_sets(const SegArgs& a, hipStream_t s) {
-    uint32_t maxseg = 0, maxk = 0;
+hipError_t launch_seg_sets(SegArgs a, hipStream_t s) {
+    uint32_t maxk = 0, maxN = 0;
+    uint64_t segs = 0;  // workgroups with one stripe each
     for (uint32_t i = 0; i < a.S; ++i) {
-        const size_t N = (size_t)a.set[i].k * a.set[i].r;
-        const uint32_t nseg = (uint32_t)((N + kSegLen - 1) / kSegLen);
-        maxseg = nseg > maxseg ? nseg : maxseg;
+        const uint32_t N = a.set[i].k * a.set[i].r;
+        segs += (uint64_t)seg_count<1>(N) * a.set[i].count;
+        maxN = N > maxN ? N : maxN;
         maxk = a.set[i].k > maxk ? a.set[i].k : maxk;
     }
     const uint32_t nv = a.S ? a.vend[a.S - 1] : 0u;
     if (nv == 0) return hipSuccess;
     if (nv > 65535u) return hipErrorInvalidValue;
-    const dim3 gseg(maxseg, nv);
-    hipLaunchKernelGGL((syn_p1<SPARSE>), gseg, dim3(kSegThreads), 0, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(syn_p2, gseg, dim3(kSegThreads), 0, s, a);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(syn_p3, dim3(ceil_div(maxk, 256u), nv), dim3(256), 0, s, a);
+    // placed by XCD: whole eights, and a rest of six or more (its empty places
+    // return at once; fewer vectors would leave XCDs idle)
+    a.by_xcd = (nv + 2) / kXcds * kXcds;
+    if (a.by_xcd > 65535u) a.by_xcd = nv / kXcds * kXcds;
+    const uint32_t rows = nv > a.by_xcd ? nv : a.by_xcd;
+    // four stripes per workgroup where one each would be more workgroups than
+    // the chip holds at once (eight per compute unit)
+    hipError_t e;
+    if (segs > 2048) {
+        const dim3 gseg(seg_count<4>(maxN), rows);
+        hipLaunchKernelGGL((syn_p1<SPARSE, 4>), gseg, dim3(kSegThreads), 0, s, a);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL((syn_p2<4>), gseg, dim3(kSegThreads), 0, s, a);
+    } else {
+        const dim3 gseg(seg_count<1>(maxN), rows);
+        hipLaunchKernelGGL((syn_p1<SPARSE, 1>), gseg, dim3(kSegThreads), 0, s, a);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL((syn_p2<1>), gseg, dim3(kSegThreads), 0, s, a);
+    }
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(syn_p3, dim3(ceil_div(maxk, 256u), rows), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
