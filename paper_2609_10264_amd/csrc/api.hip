@@ -519,6 +519,10 @@ mvk_status decode_verify_run(const mvk_key* key, const uint32_t* Xhat, const uin
     const mvk_sparse* ey = &drawn;
     uint32_t* rv = (uint32_t*)((char*)ws + e_bytes);
     uint32_t* syn_scratch = (uint32_t*)((char*)ws + e_bytes + r_bytes);
+    // few columns: no r_q at all
+    if (dv_dot_fits(*key, B, ell, ey->t, Yhat, Y))
+        return hip_status(
+            launch_decode_verify_dot(*key, Xhat, Yhat, B, *ex, *ey, syn_scratch, Y, ctrl, vL, vR, accept, s));
     if (Ny <= kSynScratchAbove &&
         dv_syn_fits(m, key->n, (uint32_t)Ny, B, ell, dv_decode_cols(m, B, key->PT, Yhat, Y, rv))) {
         // one launch: the syndromes overlap the Decrypt and Verify gathers

@@ -25,6 +25,7 @@
 #include "masks.h"
 #include "mvk_internal.h"
 #include "syn_block.h"
+#include "syn_seg.h"
 
 namespace mvk {
 
@@ -113,8 +114,9 @@ constexpr uint32_t kSpinLimit = 1u << 24;
 // the r_q are read device-coherently.
 //
 // PRE: the output mask P e_b is given (My, B x m, from client_prepare) and
-// replaces the gathers.
-template <bool WAIT_R, int G, bool PRE = false, int E = 1>
+// replaces the gathers.  VR = false: Y only (v_R comes from other workgroups,
+// which read Yhat: Y must not overlap it).
+template <bool WAIT_R, int G, bool PRE = false, int E = 1, bool VR = true>
 __device__ __forceinline__ void decode_part(const uint32_t* __restrict__ PT, uint32_t m, uint32_t Nx,
                                             const uint32_t* __restrict__ Yhat, uint32_t B,
                                             const uint32_t* __restrict__ ex_idx, const uint32_t* __restrict__ ex_val,
@@ -133,7 +135,7 @@ __device__ __forceinline__ void decode_part(const uint32_t* __restrict__ PT, uin
     uint32_t yraw[E];
     load_cols<E>(Yhat + (size_t)b * m + is, yraw);
     uint32_t rq[kPreQ][E];
-    if (!WAIT_R && g == 0) {
+    if (VR && !WAIT_R && g == 0) {
 #pragma unroll
         for (int q = 0; q < kPreQ; ++q) load_cols<E>(rv + (size_t)((uint32_t)q < ell ? q : 0) * m + is, rq[q]);
     }
@@ -185,6 +187,7 @@ __device__ __forceinline__ void decode_part(const uint32_t* __restrict__ PT, uin
         }
         if (act && Y) store_cols<E>(Y + (size_t)b * m + i0, y);
     }
+    if (!VR) return;
     if (WAIT_R) {
         if (threadIdx.x == 0) {
             uint32_t it = 0;
@@ -315,6 +318,8 @@ __device__ __forceinline__ void verify_part(const uint32_t* __restrict__ Q, uint
         verify_column(u_s, ell, B, b, Xhat[(size_t)b * n + ks], accL, nsub, cb % nsub);
 }
 
+constexpr uint32_t kFinSums = 64;
+
 // End of a decode/verify launch.  Ordering without cache-wide fences: the
 // accumulators are touched only by atomics, which are performed at the
 // device-wide coherence point.  Every wave waits for its atomics to complete
@@ -325,13 +330,42 @@ __device__ __forceinline__ void verify_part(const uint32_t* __restrict__ Q, uint
 __device__ __forceinline__ void finish(uint32_t B, uint32_t ell, uint32_t nsub, unsigned long long* accL,
                                        unsigned long long* accR, uint32_t* ctrl, uint32_t slots, uint32_t* rdone,
                                        uint32_t* err, uint32_t* __restrict__ vL, uint32_t* __restrict__ vR,
-                                       uint32_t* __restrict__ accept, uint32_t* last) {
+                                       uint32_t* __restrict__ accept, uint32_t* last, uint32_t counted = gridDim.x) {
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (threadIdx.x == 0) *last = count_last(ctrl, slots) ? 1u : 0u;
+    if (threadIdx.x == 0) *last = count_last(ctrl, slots, counted) ? 1u : 0u;
     __syncthreads();
     if (!*last) return;
     const uint32_t bad = err ? __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    if (ell * B <= kFinSums) {
+        // few sums: a thread per accumulator (one thread per column would wait
+        // for one atomic after the other), added up in LDS
+        __shared__ unsigned long long fin[2][kFinSums];
+        if (threadIdx.x < kFinSums) fin[0][threadIdx.x] = fin[1][threadIdx.x] = 0ull;
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < ell * B * nsub; i += blockDim.x) {
+            const unsigned long long l = atomicExch(&accL[i], 0ull), r = atomicExch(&accR[i], 0ull);
+            atomicAdd(&fin[0][i / nsub], l);
+            atomicAdd(&fin[1][i / nsub], r);
+        }
+        __syncthreads();
+        if (threadIdx.x < B) {
+            uint32_t ok = bad ? 0u : 1u;
+            for (uint32_t q = 0; q < ell; ++q) {
+                const uint32_t o = q * B + threadIdx.x;
+                const uint32_t L = fred64(fin[0][o]), R = fred64(fin[1][o]);
+                if (vL) vL[o] = L;
+                if (vR) vR[o] = R;
+                ok &= (L == R) ? 1u : 0u;
+            }
+            accept[threadIdx.x] = ok;
+        }
+        if (threadIdx.x == 0) {  // (every thread has read err)
+            if (rdone) atomicExch(rdone, 0u);
+            if (err) atomicExch(err, 0u);
+        }
+        return;
+    }
     for (uint32_t b = threadIdx.x; b < B; b += blockDim.x) {
         uint32_t ok = bad ? 0u : 1u;
         for (uint32_t q = 0; q < ell; ++q) {
@@ -454,6 +488,242 @@ __global__ __launch_bounds__(kFusedThreads) void decode_verify_syn(
                                                   err);
     }
     finish(B, ell, nsub, accL, accR, ctrl, slots, rdone, err, vL, vR, accept, &last);
+}
+
+// Decode/verify without the vectors r_q, for few columns.  With z the second
+// suffix sum of the syndrome of e_q (App. B),
+//   v_R[q][b] = (Gy e_q)^T Yhat_b = sum_i v1[i] z[i] Yhat_b[pi1[i] / r]
+// so a workgroup that holds z at some positions adds its share of v_R itself:
+// no scatter by Pi1, no fold, and nobody waits for a whole r_q.  The price is r
+// times as many products with Yhat, gathered, which is why this is for few
+// columns (kDotMaxB).
+//
+// Adds the sums over the workgroup of x[b] (b < kDotMaxB; columns < B) to
+// accumulator (q, b, sub).  NW waves.
+constexpr uint32_t kDotMaxB = 8;
+template <int NW>
+__device__ __forceinline__ void dot_add(const uint64_t (&x)[kDotMaxB], uint32_t B, uint32_t q, uint32_t sub,
+                                        unsigned long long* accR, uint32_t nsub, uint64_t (*red)[kDotMaxB]) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (uint32_t b = 0; b < kDotMaxB; ++b) {
+        if (b >= B) break;
+        const uint64_t w = wave_sum_u64(x[b]);
+        if (lane == 0) red[wave][b] = w;
+    }
+    __syncthreads();
+    if (threadIdx.x < B) {
+        uint64_t t = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) t += red[w][threadIdx.x];
+        atomicAdd(&accR[((size_t)q * B + threadIdx.x) * nsub + sub], (unsigned long long)fred64(t));
+    }
+}
+
+// The first suffix sum of a challenge of at most 64 terms, without an array:
+// with the terms in descending order of position in the lanes of a wave, the
+// sums at 64 consecutive positions are a few of the running sums, found with
+// two ballots.
+struct TermSums {
+    int32_t key;   // position of the lane's term, -1: none
+    uint32_t sum;  // of the values of this and the lanes before
+    // (j, v): the term of lanes < t.  N <= 2^24.
+    __device__ __forceinline__ void sort(uint32_t j, uint32_t v, uint32_t t, uint32_t N) {
+        const uint32_t lane = threadIdx.x & 63;
+        const bool has = lane < t;
+        const int32_t pos = has ? (int32_t)(j < N ? j : N - 1) : -1;
+        const int32_t uniq = pos * 64 + (int32_t)(63 - lane);  // distinct, ordered as the positions
+        uint32_t rank = 0;
+#pragma unroll
+        for (int k = 0; k < 64; ++k) rank += __builtin_amdgcn_readlane(uniq, k) > uniq ? 1u : 0u;
+        key = __builtin_amdgcn_ds_permute((int)(rank * 4), pos);  // to lane `rank`: one value to each lane
+        sum = syn::wave_incl_scan_dpp((uint32_t)__builtin_amdgcn_ds_permute((int)(rank * 4), (int)(has ? v : 0u)));
+    }
+    // the sum of the terms at positions >= c0 + lane (c0 uniform)
+    __device__ __forceinline__ uint32_t at(uint32_t c0) const {
+        const int32_t pos = (int32_t)(c0 + (threadIdx.x & 63));
+        const int after = __popcll(__ballot(key >= (int32_t)c0 + 64));  // terms behind these positions
+        const int upto = __popcll(__ballot(key >= (int32_t)c0));
+        uint32_t x = after ? (uint32_t)__builtin_amdgcn_readlane((int)sum, after - 1) : 0u;
+        for (int i = after; i < upto; ++i) {
+            const uint32_t si = (uint32_t)__builtin_amdgcn_readlane((int)sum, i);
+            x = pos <= __builtin_amdgcn_readlane(key, i) ? si : x;
+        }
+        return x;
+    }
+};
+
+// Share of v_R of positions [kFusedThreads seg, + kFusedThreads) of a block of
+// N <= kFusedThreads * U positions.  Every workgroup takes the first suffix sum
+// (from the sorted terms, ty <= kSortMax) and its products with V2 at all N
+// positions: those that Pi2 sends into the segment go to LDS, those that it
+// sends behind it are added up to the segment's carry.  That repeats N
+// products per workgroup (1.2 us of one CU at N = 12288) and takes the place
+// of a scan and two scatters of the whole block by one CU (about 10 us).
+constexpr uint32_t kSortMax = 64;
+struct DotLds {
+    uint32_t y[kFusedThreads];
+    uint64_t carry[kFusedGroups];
+    uint32_t wsum[kFusedGroups];
+    uint64_t red[kFusedGroups][kDotMaxB];
+};
+template <int U>
+__device__ __forceinline__ void syn_dot_part(uint32_t q, uint32_t seg, uint32_t m, uint32_t r, uint32_t N,
+                                             const uint32_t* __restrict__ pi1, const uint32_t* __restrict__ pi2,
+                                             const uint32_t* __restrict__ v1, const uint32_t* __restrict__ v2,
+                                             const uint32_t* __restrict__ ey_idx, const uint32_t* __restrict__ ey_val,
+                                             uint32_t ty, const uint32_t* __restrict__ Yhat, uint32_t B,
+                                             unsigned long long* accR, uint32_t nsub, DotLds& lds) {
+    constexpr uint32_t T = kFusedThreads;
+    const uint32_t tid = threadIdx.x, lane = tid & 63;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t a = seg * T, b1 = a + T < N ? a + T : N;  // (a < N)
+    // the terms first, then this thread's position of the segment (Pi1, V1 and,
+    // once Pi1 is there, Yhat), then Pi2 and V2 at every position
+    const uint32_t qt = lane < ty ? lane : 0u;
+    const uint32_t sj = ey_idx[(size_t)q * ty + qt], sv = ey_val[(size_t)q * ty + qt];
+    const bool in = a + tid < N;
+    const uint32_t is = in ? a + tid : a;
+    const uint32_t p1 = pi1[is], w1 = v1[is];
+    uint32_t p2[U], w2[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint32_t j = tid + T * u;
+        const uint32_t js = j < N ? j : 0u;
+        p2[u] = pi2[js];
+        w2[u] = v2[js];
+    }
+    TermSums S;  // (every wave for itself)
+    S.sort(sj, sv, ty, N);
+    lds.y[tid] = 0u;
+    const uint32_t row = (p1 < N ? p1 : N - 1) / r;  // < m
+    uint32_t yv[kDotMaxB];
+#pragma unroll
+    for (uint32_t b = 0; b < kDotMaxB; ++b) yv[b] = b < B ? Yhat[(size_t)b * m + row] : 0u;
+    __syncthreads();
+    uint64_t carry = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (T * u >= N) break;  // (uniform)
+        const uint32_t y = fmul(w2[u], S.at(64 * wave + T * u));
+        if (tid + T * u < N) {
+            const uint32_t p = p2[u] < N ? p2[u] : N - 1;
+            if (p >= b1) carry += y;
+            else if (p >= a) lds.y[p - a] = y;
+        }
+    }
+    carry = wave_sum_u64(carry);
+    if (lane == 0) lds.carry[wave] = carry;
+    __syncthreads();
+    // second suffix sum of the segment: one position per thread
+    const uint32_t x = lds.y[tid];
+    const uint32_t incl = syn::wave_incl_scan_dpp(x);
+    if (lane == 63) lds.wsum[wave] = incl;
+    __syncthreads();
+    uint64_t after = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kFusedGroups; ++w) after += lds.carry[w] + (w > wave ? lds.wsum[w] : 0u);
+    const uint32_t z = fadd(fadd(x, fsub(lds.wsum[wave], incl)), fred64(after));
+    const uint32_t c = in ? fmul(w1, z) : 0u;
+    uint64_t t[kDotMaxB];
+#pragma unroll
+    for (uint32_t b = 0; b < kDotMaxB; ++b) t[b] = ffold((uint64_t)c * yv[b]);
+    dot_add<kFusedGroups>(t, B, q, seg % nsub, accR, nsub, lds.red);
+}
+
+// One launch for blocks of up to kFusedThreads * U positions: workgroups
+// [0, ell nseg) add up v_R (syn_dot_part), the next nblkL v_L (verify role),
+// the rest decrypt (Y only; they add nothing and do not count).
+template <int U>
+__global__ __launch_bounds__(kFusedThreads) void decode_verify_dot(
+    const uint32_t* __restrict__ PT, const uint32_t* __restrict__ Q, uint32_t m, uint32_t n, uint32_t Nx,
+    uint32_t Ny, const uint32_t* __restrict__ Xhat, const uint32_t* __restrict__ Yhat, uint32_t B,
+    const uint32_t* __restrict__ ex_idx, const uint32_t* __restrict__ ex_val, uint32_t tx,
+    const uint32_t* __restrict__ ey_idx, const uint32_t* __restrict__ ey_val, uint32_t ty, uint32_t ell,
+    uint32_t cyr, const uint32_t* __restrict__ pi1, const uint32_t* __restrict__ pi2,
+    const uint32_t* __restrict__ v1, const uint32_t* __restrict__ v2, uint32_t* __restrict__ Y,
+    unsigned long long* accL, unsigned long long* accR, uint32_t nsub, uint32_t nblkR, uint32_t nblkL,
+    uint32_t nseg, uint32_t* ctrl, uint32_t slots, uint32_t* __restrict__ vL, uint32_t* __restrict__ vR,
+    uint32_t* __restrict__ accept) {
+    constexpr size_t kWords = kGatherWords > kDecodeWords ? kGatherWords : kDecodeWords;
+    __shared__ __align__(16) uint32_t lds[kWords];
+    static_assert(sizeof(DotLds) <= sizeof(lds), "the roles share the LDS");
+    __shared__ uint32_t last;
+    const uint32_t bid = blockIdx.x, ndot = ell * nseg, counted = ndot + nblkL;
+    if (bid >= counted) {
+        const uint32_t d = bid - counted;
+        decode_part<false, kFusedGroups, false, 1, false>(PT, m, Nx, Yhat, B, ex_idx, ex_val, tx, nullptr, ell, Y,
+                                                          nullptr, nsub, d / nblkR, d % nblkR,
+                                                          reinterpret_cast<uint64_t*>(lds), nullptr, nullptr);
+        return;
+    }
+    if (bid < ndot)
+        syn_dot_part<U>(bid / nseg, bid % nseg, m, cyr, Ny, pi1, pi2, v1, v2, ey_idx, ey_val, ty, Yhat, B, accR, nsub,
+                        *reinterpret_cast<DotLds*>(lds));
+    else
+        verify_part<kFusedGroups>(Q, n, Ny, Xhat, B, ey_idx, ey_val, ty, ell, accL, nsub, bid - ndot,
+                                  reinterpret_cast<uint64_t (*)[kCols]>(lds),
+                                  reinterpret_cast<uint32_t (*)[kCols]>(lds + 2 * kItems * kCols));
+    finish(B, ell, nsub, accL, accR, ctrl, slots, nullptr, nullptr, vL, vR, accept, &last, counted);
+}
+
+// Longer blocks, two launches.  The first: p1 of the syndromes (segments of
+// kSegLen positions, syn_seg.h), beside the verify and decrypt roles, which
+// need none of it.  The second: p2, each workgroup adding its share of v_R in
+// place of the scatter by Pi1; the last one compares.  (accL is complete when
+// the second starts; only the second counts.)
+template <int E>
+__global__ __launch_bounds__(kB) void decode_verify_long1(
+    const synseg::SegSet S, const uint32_t* __restrict__ PT, const uint32_t* __restrict__ Q, uint32_t m, uint32_t n,
+    uint32_t Nx, const uint32_t* __restrict__ Xhat, const uint32_t* __restrict__ Yhat, uint32_t B,
+    const uint32_t* __restrict__ ex_idx, const uint32_t* __restrict__ ex_val, uint32_t tx, uint32_t* __restrict__ Y,
+    unsigned long long* accL, uint32_t nsub, uint32_t nblkR, uint32_t nblkL, uint32_t nseg) {
+    constexpr size_t kDec = sizeof(uint64_t) * kGroups * E * 64, kVer = kGatherWords * 4, kSeg = sizeof(synseg::SegLds<1>);
+    __shared__ __align__(16) uint8_t lds[kDec > kVer ? (kDec > kSeg ? kDec : kSeg) : (kVer > kSeg ? kVer : kSeg)];
+    const uint32_t bid = blockIdx.x, nsyn = S.count * nseg;
+    if (bid < nsyn) {
+        synseg::seg_first<true, 1>(S, bid / nseg, bid % nseg, *reinterpret_cast<synseg::SegLds<1>*>(lds));
+    } else if (bid < nsyn + nblkL) {
+        verify_part<kGroups>(Q, n, S.k * S.r, Xhat, B, S.idx, S.val, S.t, S.count, accL, nsub, bid - nsyn,
+                             reinterpret_cast<uint64_t (*)[kCols]>(lds),
+                             reinterpret_cast<uint32_t (*)[kCols]>(lds + sizeof(uint64_t) * kItems * kCols));
+    } else {
+        const uint32_t d = bid - nsyn - nblkL;
+        decode_part<false, kGroups, false, E, false>(PT, m, Nx, Yhat, B, ex_idx, ex_val, tx, nullptr, S.count, Y,
+                                                     nullptr, nsub, d / nblkR, d % nblkR,
+                                                     reinterpret_cast<uint64_t*>(lds), nullptr, nullptr);
+    }
+}
+
+__global__ __launch_bounds__(synseg::kSegThreads) void decode_verify_long2(
+    const synseg::SegSet S, uint32_t m, const uint32_t* __restrict__ Yhat, uint32_t B, unsigned long long* accL,
+    unsigned long long* accR, uint32_t nsub, uint32_t nseg, uint32_t* ctrl, uint32_t slots,
+    uint32_t* __restrict__ vL, uint32_t* __restrict__ vR, uint32_t* __restrict__ accept) {
+    constexpr int P = synseg::kSegPer;
+    __shared__ synseg::SegLds<1> lds;
+    __shared__ uint64_t red[synseg::kSegThreads / 64][kDotMaxB];
+    __shared__ uint32_t last;
+    const uint32_t q = blockIdx.x / nseg, N = S.k * S.r;
+    uint32_t x[1][P], p1[1][P], w1[1][P];
+    const uint32_t sg = synseg::seg_second_load<1>(S, q, lds, x, p1, w1);
+    uint32_t yv[P][kDotMaxB];
+#pragma unroll
+    for (int e = 0; e < P; ++e) {
+        const uint32_t row = (p1[0][e] < N ? p1[0][e] : N - 1) / S.r;  // < m
+#pragma unroll
+        for (uint32_t b = 0; b < kDotMaxB; ++b) yv[e][b] = b < B ? Yhat[(size_t)b * m + row] : 0u;
+    }
+    synseg::seg_second_scan<1>(S, q, sg, lds, x);
+    const uint32_t j0 = sg * synseg::kSegLen + threadIdx.x * P;
+    uint64_t t[kDotMaxB] = {};
+#pragma unroll
+    for (int e = 0; e < P; ++e) {
+        const uint32_t c = j0 + e < N ? fmul(w1[0][e], x[0][e]) : 0u;
+#pragma unroll
+        for (uint32_t b = 0; b < kDotMaxB; ++b) t[b] += ffold((uint64_t)c * yv[e][b]);
+    }
+    dot_add<synseg::kSegThreads / 64>(t, B, q, sg % nsub, accR, nsub, red);
+    finish(B, S.count, nsub, accL, accR, ctrl, slots, nullptr, nullptr, vL, vR, accept, &last);
 }
 
 // decode_verify_masked for small problems, by a few workgroups (at most 8):
@@ -1063,6 +1333,64 @@ hipError_t launch_decode_verify_syn(const uint32_t* PT, const uint32_t* Q, uint3
     else { MVK_DVS_E(32); }
 #undef MVK_DVS_E
 #undef MVK_DVS
+    return hipGetLastError();
+}
+
+bool dv_dot_fits(const mvk_key& key, uint32_t B, uint32_t ell, uint32_t ty, const uint32_t* Yhat, const uint32_t* Y) {
+    const uint64_t Ny = (uint64_t)key.cy.r * key.m;
+    if (B == 0 || B > kDotMaxB || ell == 0 || ell > 4) return false;
+    if (Ny <= kSynScratchAbove && ty > kSortMax) return false;
+    const uintptr_t y = (uintptr_t)Y, h = (uintptr_t)Yhat, bytes = (uintptr_t)B * key.m * 4;
+    if (Y && y < h + bytes && h < y + bytes) return false;  // Y over Yhat: the columns must be read before
+    const uint64_t grid = ell * ((Ny + kFusedThreads - 1) / kFusedThreads) + ceil_div(key.n, kCols) +
+                          (uint64_t)B * ceil_div(key.m, kCols);
+    return grid <= 0x7fffffffu;
+}
+
+hipError_t launch_decode_verify_dot(const mvk_key& key, const uint32_t* Xhat, const uint32_t* Yhat, uint32_t B,
+                                    const mvk_sparse& ex, const mvk_sparse& ey, uint32_t* syn_scratch, uint32_t* Y,
+                                    uint32_t* ctrl, uint32_t* vL, uint32_t* vR, uint32_t* accept, hipStream_t s) {
+    const uint32_t m = key.m, n = key.n, ell = ey.count, Nx = key.cx.r * n, Ny = key.cy.r * m;
+    const mvk_code& c = key.cy;
+    const DvLayout l = dv_layout(m, n, B, ell);
+    unsigned long long* accL = reinterpret_cast<unsigned long long*>(ctrl + l.acc_word);
+    unsigned long long* accR = accL + (size_t)ell * B * l.nsub;
+    const uint32_t nblkL = ceil_div(n, kCols);
+    if (Ny <= kSynScratchAbove) {
+        const uint32_t U = dv_syn_u(Ny);
+        if (U == 0) return hipErrorInvalidValue;
+        const uint32_t nseg = ceil_div(Ny, (uint32_t)kFusedThreads), counted = ell * nseg + nblkL;
+        const uint32_t nblkR = ceil_div(m, kCols);
+        uint32_t slots = count_slots(counted);
+        if (slots > l.slots) slots = l.slots;  // the layout holds this many counters
+        const dim3 grid(counted + (Y ? B * nblkR : 0u));
+#define MVK_DOT(UU)                                                                                              \
+    hipLaunchKernelGGL((decode_verify_dot<UU>), grid, dim3(kFusedThreads), 0, s, key.PT, key.Q, m, n, Nx, Ny,     \
+                       Xhat, Yhat, B, ex.idx, ex.val, ex.t, ey.idx, ey.val, ey.t, ell, c.r, c.pi1, c.pi2, c.v1,   \
+                       c.v2, Y, accL, accR, l.nsub, nblkR, nblkL, nseg, ctrl, slots, vL, vR, accept)
+        if (U == 8) MVK_DOT(8);
+        else if (U == 16) MVK_DOT(16);
+        else if (U == 24) MVK_DOT(24);
+        else MVK_DOT(32);
+#undef MVK_DOT
+        return hipGetLastError();
+    }
+    const uint32_t nseg = ceil_div(Ny, synseg::kSegLen);
+    const uint32_t E = dv_decode_cols(m, B, key.PT, Yhat, Y, key.PT), nblkR = ceil_div(m, kCols * E);
+    const synseg::SegSet S{c.pi1, c.pi2, c.v1, c.v2, nullptr, ey.idx, ey.val, nullptr, nullptr, syn_scratch,
+                           c.k,   c.r,   ey.t, ell};
+    const dim3 grid1(ell * nseg + nblkL + (Y ? B * nblkR : 0u));
+#define MVK_LONG(EE)                                                                                             \
+    hipLaunchKernelGGL((decode_verify_long1<EE>), grid1, dim3(kB), 0, s, S, key.PT, key.Q, m, n, Nx, Xhat, Yhat, \
+                       B, ex.idx, ex.val, ex.t, Y, accL, l.nsub, nblkR, nblkL, nseg)
+    if (E == 4) MVK_LONG(4); else MVK_LONG(1);
+#undef MVK_LONG
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    uint32_t slots = count_slots(ell * nseg);
+    if (slots > l.slots) slots = l.slots;
+    hipLaunchKernelGGL(decode_verify_long2, dim3(ell * nseg), dim3(synseg::kSegThreads), 0, s, S, m, Yhat, B, accL,
+                       accR, l.nsub, nseg, ctrl, slots, vL, vR, accept);
     return hipGetLastError();
 }
 

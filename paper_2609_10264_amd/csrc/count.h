@@ -37,9 +37,9 @@ __host__ __device__ inline uint32_t count_words(uint32_t slots) { return kCountS
 // true in exactly one workgroup, the last to arrive; the counters it used are
 // reset before it returns.  Each decision waits for the atomic it depends on,
 // so everything that completed before any workgroup's count is visible to
-// device-coherent reads of the last one.
-__device__ inline bool count_last(uint32_t* ctrl, uint32_t slots) {
-    const uint32_t grid = gridDim.x;
+// device-coherent reads of the last one.  `grid`: the workgroups that count,
+// those of the lowest indices (all of them unless some have nothing to add).
+__device__ inline bool count_last(uint32_t* ctrl, uint32_t slots, uint32_t grid = gridDim.x) {
     if (slots == 0) {
         if (atomicAdd(ctrl, 1u) != grid - 1) return false;
         atomicExch(ctrl, 0u);

@@ -130,6 +130,16 @@ hipError_t launch_decode_verify_syn(const uint32_t* PT, const uint32_t* Q, uint3
                                     const uint32_t* v2, uint32_t* r, uint32_t* Y, uint32_t* ctrl, uint32_t* vL,
                                     uint32_t* vR, uint32_t* accept, hipStream_t s);
 
+// Decrypt + Verify without the vectors r_q (client.hip): one launch up to
+// kSynScratchAbove positions, two above, with syn_scratch of
+// syn_scratch_bytes(ey.count, Ny).  Y may be null; ctrl as above.
+// dv_dot_fits: few columns and repetitions, challenges short enough to sort
+// (blocks up to kSynScratchAbove), and Y apart from Yhat.
+bool dv_dot_fits(const mvk_key& key, uint32_t B, uint32_t ell, uint32_t ty, const uint32_t* Yhat, const uint32_t* Y);
+hipError_t launch_decode_verify_dot(const mvk_key& key, const uint32_t* Xhat, const uint32_t* Yhat, uint32_t B,
+                                    const mvk_sparse& ex, const mvk_sparse& ey, uint32_t* syn_scratch, uint32_t* Y,
+                                    uint32_t* ctrl, uint32_t* vL, uint32_t* vR, uint32_t* accept, hipStream_t s);
+
 // decode_verify with the output masks My (B x m) and the vectors u_q (U,
 // ell x n) from client_prepare in place of the gathers.
 hipError_t launch_decode_verify_masked(uint32_t m, uint32_t n, const uint32_t* Xhat, const uint32_t* Yhat,

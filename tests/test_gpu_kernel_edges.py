@@ -86,3 +86,41 @@ def test_prepare_split(m, n, rx, ry, B, tx, p):
     R = oracle.encode(t.cy, np.zeros((2, m), dtype=np.uint32), t.eyi, t.eyv, p=p)
     assert np.array_equal(host(prep.R), R)
     assert np.array_equal(host(prep.U), oracle.server_eval(np.ascontiguousarray(t.W.T), R, p=p))
+
+
+# Decode/verify without r_q (up to 8 columns, 4 repetitions and, in short blocks,
+# 64 terms): no noise, the most terms and one more; N around one segment
+# of 512 and of 1024 positions, 16384 (the last block of one workgroup) and one
+# more, long blocks with four columns per lane; the next column and repetition;
+# Y over Yhat.
+@pytest.mark.parametrize("m,n,rx,ry,B,tx,ty,ell,inplace", [
+    (1, 1, 1, 1, 1, 0, 1, 1, False), (5, 3, 2, 3, 3, 6, 15, 4, False), (256, 256, 2, 2, 1, 8, 31, 2, False),
+    (257, 300, 2, 2, 8, 64, 64, 2, False), (171, 100, 3, 3, 2, 65, 65, 3, False), (1000, 700, 3, 4, 4, 128, 129, 2, False),
+    (500, 500, 3, 1, 1, 192, 192, 1, False), (600, 400, 3, 3, 1, 193, 193, 1, False), (300, 500, 2, 3, 9, 20, 31, 2, False),
+    (300, 500, 2, 3, 2, 20, 31, 5, False), (300, 500, 2, 3, 2, 20, 31, 2, True), (4096, 200, 3, 4, 1, 63, 63, 2, False),
+    (4097, 200, 3, 4, 1, 63, 63, 2, False), (5462, 4097, 4, 3, 3, 40, 31, 2, False), (8192, 5000, 4, 8, 8, 154, 200, 4, False),
+    (9001, 300, 2, 2, 2, 30, 31, 2, True), (16384, 1000, 3, 8, 4, 8, 31, 2, False),
+])
+@pytest.mark.parametrize("p", [synth.P, synth.P_BABYBEAR])
+def test_few_terms_few_columns(m, n, rx, ry, B, tx, ty, ell, inplace, p):
+    from tests.gpu_util import Instance
+    print("decode", m, n, rx, ry, B, tx, ty, ell, inplace, p, flush=True)
+    t = Instance(560 + m + ty, m, n, B, rx, tx, ty, ell, ry=ry, p=p)
+    t.to_device()
+    mvk.keygen(t.key, t.dW)
+    xh = mvk.encode(t.key, t.dX, t.dexi, t.dexv)
+    assert np.array_equal(host(xh), oracle.encode(t.cx, t.X, t.exi, t.exv, p=p))
+    yh = mvk.server_eval(t.dW, xh, p=p)
+    yh[B - 1, m - 1] = (yh[B - 1, m - 1].long() + 1).remainder(p).int()  # the last column is wrong
+    hyh = host(yh)
+    PT, Q = host(t.key.PT), host(t.key.Q)
+    acc0, vL0, vR0 = oracle.verify(t.cy, Q, host(xh), hyh, t.eyi, t.eyv, p=p)
+    for _ in range(2):  # the control region is left as it was found
+        out = yh.clone()
+        vL = torch.empty((ell, B), dtype=torch.int32, device="cuda")
+        vR = torch.empty_like(vL)
+        Y, acc, _, _ = mvk.decode_verify(t.key, xh, out, t.dexi, t.dexv, t.deyi, t.deyv, Y=out if inplace else None,
+                                         vL=vL, vR=vR)
+        assert np.array_equal(host(vL), vL0) and np.array_equal(host(vR), vR0)
+        assert host(acc).tolist() == acc0.astype(np.uint32).tolist()
+        assert np.array_equal(host(Y), oracle.decode(PT, hyh, t.exi, t.exv, p=p))
