@@ -904,9 +904,12 @@ mvk_status mvk_batch_verify(const mvk_code* cy, const mvk_code* c2, const uint32
     const uint32_t ell = e->count, ell2 = e2->count;
     hipStream_t s = (hipStream_t)stream;
     const size_t r_bytes = align_up((size_t)ell * m * 4), rs_bytes = align_up((size_t)ell2 * Bn * 4);
-    size_t syn_bytes = 0;
-    syn_bytes = syn_scratch_bytes(ell, N);
-    if (syn_scratch_bytes(ell2, N2) > syn_bytes) syn_bytes = syn_scratch_bytes(ell2, N2);
+    // Primary syndromes R_q = G e_q and secondary syndromes r_j = G' e'_j: where
+    // either is long, both by segments in one sequence of launches (four claims
+    // of 4096 x 4096: the short one took 10 us by itself), else one launch each.
+    SynSet sets[2] = {{cy, e->idx, e->val, e->t, ell, nullptr}, {c2, e2->idx, e2->val, e2->t, ell2, nullptr}};
+    const bool by_seg = N > kSynScratchAbove || N2 > kSynScratchAbove;
+    const size_t syn_bytes = by_seg ? syn_sets_scratch_bytes(sets, 2) : 0;
     void* ws = nullptr;
     uint32_t* ctrl = nullptr;
     st = workspace(s, r_bytes + rs_bytes + syn_bytes, &ws, &ctrl, batch_ctrl_bytes(m, n, B, ell, ell2));
@@ -914,9 +917,15 @@ mvk_status mvk_batch_verify(const mvk_code* cy, const mvk_code* c2, const uint32
     uint32_t* R = (uint32_t*)ws;
     uint32_t* Rs = (uint32_t*)((char*)ws + r_bytes);
     uint32_t* scratch = (uint32_t*)((char*)ws + r_bytes + rs_bytes);
-    // primary syndromes R_q = G e_q and secondary syndromes r_j = G' e'_j
-    hipError_t err = launch_syn_sparse(*cy, e->idx, e->val, e->t, ell, nullptr, scratch, R, s);
-    if (err == hipSuccess) err = launch_syn_sparse(*c2, e2->idx, e2->val, e2->t, ell2, nullptr, scratch, Rs, s);
+    sets[0].out = R;
+    sets[1].out = Rs;
+    hipError_t err;
+    if (by_seg) {
+        err = launch_syn_sets(sets, 2, scratch, syn_bytes, s);
+    } else {
+        err = launch_syn_sparse(*cy, e->idx, e->val, e->t, ell, nullptr, scratch, R, s);
+        if (err == hipSuccess) err = launch_syn_sparse(*c2, e2->idx, e2->val, e2->t, ell2, nullptr, scratch, Rs, s);
+    }
     if (err == hipSuccess)
         err = launch_batch_check(m, n, B, X, Y, Ut, R, Rs, Qaux, (uint32_t)N, (uint32_t)N2, e->idx, e->val, e->t, ell,
                                  e2->idx, e2->val, e2->t, ell2, ctrl, vL, vR, sL, sR, accept, s);

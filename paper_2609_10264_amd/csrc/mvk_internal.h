@@ -62,11 +62,11 @@ constexpr size_t kSynScratchAbove = 16384;
 constexpr size_t kSynSegLen = 1024;
 // Two work arrays of N words per vector, then per vector a ticket word and one
 // status word per segment (64-bit each).
-inline size_t syn_scratch_bytes(size_t count, size_t N) {
-    if (N <= kSynScratchAbove) return 0;
+inline size_t syn_seg_bytes(size_t count, size_t N) {
     const size_t nseg = (N + kSynSegLen - 1) / kSynSegLen;
     return count * (2 * N * sizeof(uint32_t) + (nseg + 1) * sizeof(uint64_t));
 }
+inline size_t syn_scratch_bytes(size_t count, size_t N) { return N <= kSynScratchAbove ? 0 : syn_seg_bytes(count, N); }
 // G v for `count` vectors: dense (v: count x N) or sparse (idx/val: count x t).
 // If X != nullptr the result is added to X (out = X + G v), as in Encrypt.
 // scratch: syn_scratch_bytes(count, N), 8-byte aligned.
@@ -75,8 +75,8 @@ hipError_t launch_syn_dense(const mvk_code& c, const uint32_t* v, uint32_t count
 hipError_t launch_syn_sparse(const mvk_code& c, const uint32_t* idx, const uint32_t* val, uint32_t t,
                              uint32_t count, const uint32_t* X, uint32_t* scratch, uint32_t* out,
                              hipStream_t s);
-// Sparse syndromes of long blocks (N > kSynScratchAbove) of several codes in
-// one sequence of three launches: set i is `count` vectors (idx/val: count x
+// Sparse syndromes of several codes, by segments whatever their length, in one
+// sequence of three launches: set i is `count` vectors (idx/val: count x
 // t) over code *c, results into out (count x c->k).  scratch: scratch_bytes
 // of at least syn_sets_scratch_bytes(sets, S), 256-byte aligned (else
 // hipErrorInvalidValue and nothing is launched).

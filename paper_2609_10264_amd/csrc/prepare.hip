@@ -453,6 +453,7 @@ struct PrepPlan {
     uint64_t grid;        // workgroups of the launch (of the gather launch when split)
     uint64_t syn_groups;  // syndrome workgroups
     bool split;           // syndromes and gathers in two launches (client_gather_kernel)
+    bool join;            // every syndrome runs by segments, with the long ones
     bool wide;            // the gather launch's items are kWideCols columns wide
 };
 
@@ -475,6 +476,7 @@ PrepPlan plan_with_cols(PrepPlan pl, const PrepInputDesc* ins, uint32_t NI, cons
                         uint32_t cols) {
     PrepArgs& a = pl.a;
     uint64_t sx = 0, sy = 0, items = 0;
+    bool any_long = false;
     for (uint32_t j = 0; j < NI; ++j) {
         const PrepInputDesc& d = ins[j];
         PrepIn& in = a.in[j];
@@ -483,6 +485,7 @@ PrepPlan plan_with_cols(PrepPlan pl, const PrepInputDesc* ins, uint32_t NI, cons
         in.idx = d.idx, in.val = d.val, in.Mx = d.Mx;
         in.n = c->k, in.r = c->r, in.t = d.t, in.count = d.count;
         const uint64_t N = (uint64_t)c->k * c->r;
+        any_long = any_long || (d.count && !prep_short(N));
         if (d.count && prep_short(N)) {
             sx += d.count;
             pl.U = prep_u(N) > pl.U ? prep_u(N) : pl.U;
@@ -504,6 +507,7 @@ PrepPlan plan_with_cols(PrepPlan pl, const PrepInputDesc* ins, uint32_t NI, cons
         const uint64_t ix = (uint64_t)nx * pr.nbm, iy = (uint64_t)d.count * pr.nbn;
         pr.items_x = (uint32_t)(ix < 0xffffffffu ? ix : 0xffffffffu);
         const uint64_t N = (uint64_t)key.m * key.cy.r;
+        any_long = any_long || (d.count && !prep_short(N));
         if (d.count && prep_short(N)) {
             sy += d.count;
             pl.U = prep_u(N) > pl.U ? prep_u(N) : pl.U;
@@ -516,6 +520,11 @@ PrepPlan plan_with_cols(PrepPlan pl, const PrepInputDesc* ins, uint32_t NI, cons
     // launch of small workgroups (client_gather_kernel), after the syndromes
     pl.syn_groups = sy;
     pl.split = (items + kQuarters - 1) / kQuarters > 256;
+    // In a split plan the short syndromes are a launch of their own, about 10 us
+    // of a few compute units each.  Where long ones run by segments anyway the
+    // short ones join them, up to as many as there are compute units (above,
+    // they fill the chip by themselves and their work arrays would grow large).
+    pl.join = pl.split && any_long && sy <= 256;
     pl.grid = pl.split ? items : sy + (items + kQuarters - 1) / kQuarters;
     pl.wide = cols == kWideCols;
     if (pl.split && pl.vec && !pl.wide) {
@@ -535,15 +544,17 @@ size_t prep_ctrl_words(const PrepInputDesc* ins, uint32_t NI, const PrepProbDesc
 static_assert(2 * kMaxPrep <= kMaxSynSets, "one syndrome set per input and per key");
 
 namespace {
-// The syndromes too long for one workgroup: noise of the inputs, then
-// challenges of the keys (one set each).
-uint32_t long_sets(const PrepInputDesc* ins, uint32_t NI, const PrepProbDesc* probs, uint32_t G, SynSet* sets) {
+// The syndromes that run by segments, before the rest (those too long for one
+// workgroup, or with `join` all of them): noise of the inputs, then challenges
+// of the keys (one set each).
+uint32_t seg_sets(const PrepInputDesc* ins, uint32_t NI, const PrepProbDesc* probs, uint32_t G, bool join,
+                  SynSet* sets) {
     uint32_t S = 0;
     for (uint32_t j = 0; j < NI; ++j)
-        if (ins[j].count && !prep_short((uint64_t)ins[j].cx->k * ins[j].cx->r))
+        if (ins[j].count && (join || !prep_short((uint64_t)ins[j].cx->k * ins[j].cx->r)))
             sets[S++] = SynSet{ins[j].cx, ins[j].idx, ins[j].val, ins[j].t, ins[j].count, ins[j].Mx};
     for (uint32_t g = 0; g < G; ++g)
-        if (probs[g].count && !prep_short((uint64_t)probs[g].key->m * probs[g].key->cy.r))
+        if (probs[g].count && (join || !prep_short((uint64_t)probs[g].key->m * probs[g].key->cy.r)))
             sets[S++] = SynSet{&probs[g].key->cy, probs[g].idx, probs[g].val, probs[g].t, probs[g].count, probs[g].R};
     return S;
 }
@@ -551,26 +562,25 @@ uint32_t long_sets(const PrepInputDesc* ins, uint32_t NI, const PrepProbDesc* pr
 
 size_t prep_scratch_bytes(const PrepInputDesc* ins, uint32_t NI, const PrepProbDesc* probs, uint32_t G) {
     SynSet sets[2 * kMaxPrep];
-    return syn_sets_scratch_bytes(sets, long_sets(ins, NI, probs, G, sets));
+    return syn_sets_scratch_bytes(sets, seg_sets(ins, NI, probs, G, prep_plan(ins, NI, probs, G).join, sets));
 }
 
 hipError_t launch_client_prepare_multi(const PrepInputDesc* ins, uint32_t NI, const PrepProbDesc* probs, uint32_t G,
                                        uint32_t* scratch, size_t scratch_bytes, uint32_t* counter,
                                        uint32_t* const* done, uint32_t ndone, uint32_t done_value, hipStream_t s) {
     if (NI > kMaxPrep || G == 0 || G > kMaxPrep || ndone > kMaxPrep) return hipErrorInvalidValue;
-    // syndromes too long for one workgroup run first, all of them in one
-    // sequence of segmented launches
+    PrepPlan pl = prep_plan(ins, NI, probs, G);
+    // syndromes by segments run first, all of them in one sequence of launches
     SynSet sets[2 * kMaxPrep];
-    const uint32_t S = long_sets(ins, NI, probs, G, sets);
+    const uint32_t S = seg_sets(ins, NI, probs, G, pl.join, sets);
     if (S) {
         const hipError_t e = launch_syn_sets(sets, S, scratch, scratch_bytes, s);
         if (e != hipSuccess) return e;
     }
-    PrepPlan pl = prep_plan(ins, NI, probs, G);
     if (pl.grid == 0) return hipSuccess;
     if (pl.grid > 0x7fffffffu) return hipErrorInvalidValue;
     PrepArgs& a = pl.a;
-    if (pl.split && pl.syn_groups) {
+    if (pl.split && pl.syn_groups && !pl.join) {
         // the short syndromes: client_prepare_kernel with their workgroups only
         // (complete, and visible to the gather launch, when it ends)
         const dim3 sgrid((uint32_t)pl.syn_groups), sblock(kPrepThreads);

@@ -763,7 +763,7 @@ hipError_t launch_encT_i8(const mvk_code& c, const int8_t* in, size_t ld_in, siz
 
 size_t syn_sets_scratch_bytes(const SynSet* sets, uint32_t S) {
     size_t b = 0;
-    for (uint32_t i = 0; i < S; ++i) b += (syn_scratch_bytes(sets[i].count, (size_t)sets[i].c->k * sets[i].c->r) + 255) & ~(size_t)255;
+    for (uint32_t i = 0; i < S; ++i) b += (syn_seg_bytes(sets[i].count, (size_t)sets[i].c->k * sets[i].c->r) + 255) & ~(size_t)255;
     return b;
 }
 
@@ -777,13 +777,12 @@ hipError_t launch_syn_sets(const SynSet* sets, uint32_t S, uint32_t* scratch, si
     for (uint32_t i = 0; i < S; ++i) {
         const SynSet& d = sets[i];
         const size_t N = (size_t)d.c->k * d.c->r;
-        if (N <= kSynScratchAbove) return hipErrorInvalidValue;  // long blocks only
         if (d.count == 0) continue;
         a.set[a.S] = SegSet{d.c->pi1, d.c->pi2, d.c->v1, d.c->v2, nullptr, d.idx, d.val, nullptr, d.out,
                             reinterpret_cast<uint32_t*>(w), d.c->k, d.c->r, d.t, d.count};
         nv += d.count;
         a.vend[a.S++] = nv;
-        w += (syn_scratch_bytes(d.count, N) + 255) & ~(size_t)255;
+        w += (syn_seg_bytes(d.count, N) + 255) & ~(size_t)255;
     }
     return launch_seg_sets<true>(a, s);
 }
