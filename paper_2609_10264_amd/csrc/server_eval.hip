@@ -1289,15 +1289,20 @@ GroupPlan group_plan(uint32_t m, uint32_t n, uint32_t nb) {
     // digits-stationary: rows 128*tww, each k-range's digit tiles fit in LDS;
     // estimated time ceil(workgroups / 256) * (W k-blocks per workgroup in units
     // of 128 rows + fill + exchange of the split values, which the last
-    // workgroup of a row block reads from the ks - 1 others)
+    // workgroup of a row block reads from the ks - 1 others).  The exchange is
+    // in proportion to the row blocks that do it at a time, up to 64: sweeps of
+    // ks on MI355X, 16 queries: 256 x 4096 6.8 us with eight ranges against 8.9
+    // with four, 1024 x 4096 7.3 against 9.3, 2048 x 2048 7.2 with four against
+    // 9.5 with two; 4096 x 4096 10.4 with eight and 10.6 with four.
     const uint32_t kbm = qt == 4 ? kDstatKbm4 : kDstatKbm2;
-    uint32_t best = 0xffffffffu;
+    uint64_t best = ~0ull;
     for (uint32_t tww = 1; tww <= 2; ++tww)
         for (uint32_t ks = 1; ks <= 8; ks *= 2) {
             const uint32_t kb_per = ceil_div(nkb, ks);
             if (kb_per > kbm) continue;
-            const uint32_t rows = 128 * tww, nwg = ceil_div(m, rows) * ks;
-            const uint32_t cost = ceil_div(nwg, 256) * (kb_per * tww + 6 + qt * (ks - 1));
+            const uint32_t rows = 128 * tww, nrb = ceil_div(m, rows), nwg = nrb * ks;
+            const uint64_t cost = (uint64_t)ceil_div(nwg, 256) *
+                                  (64 * (kb_per * tww + 6) + qt * (ks - 1) * (nrb < 64 ? nrb : 64));
             if (cost < best) {
                 best = cost;
                 g = GroupPlan{true, qt, tww, rows, ks, dstat_kbm(kb_per)};

@@ -124,3 +124,18 @@ def test_few_terms_few_columns(m, n, rx, ry, B, tx, ty, ell, inplace, p):
         assert np.array_equal(host(vL), vL0) and np.array_equal(host(vR), vR0)
         assert host(acc).tolist() == acc0.astype(np.uint32).tolist()
         assert np.array_equal(host(Y), oracle.decode(PT, hyh, t.exi, t.exv, p=p))
+
+
+# Eight k-ranges of the digits-stationary kernel where there are few row blocks:
+# ranges that are empty or cut short, one row, the last row block of that rule.
+@pytest.mark.parametrize("m,n,B", [(1, 300, 5), (100, 577, 16), (256, 4096, 8), (256, 4096, 16), (1000, 4100, 12),
+                                   (2048, 2048, 16), (4096, 4096, 8), (8064, 640, 9)])
+@pytest.mark.parametrize("p", [synth.P, synth.P_BABYBEAR])
+def test_many_k_ranges(m, n, B, p):
+    W = synth.weights(700 + m + n, m, n, lo=-128)
+    X = synth.field_uniform(701 + B + n, (B, n), p=p)
+    print("k-ranges", m, n, B, p, flush=True)
+    want = oracle.server_eval(W, X, p=p, nthreads=oracle.threads())
+    for dW in (dev(W), mvk.pack_weights(dev(W))):
+        for _ in range(2):
+            assert np.array_equal(host(mvk.server_eval(dW, dev(X), p=p)), want)
