@@ -33,19 +33,27 @@ __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
     return v;
 }
 
-// Sum of one value per thread over the workgroup, added into *acc (64-bit
-// atomics: exact, so the order of the additions does not matter).
-__device__ __forceinline__ void block_add(uint64_t v, uint64_t* red, unsigned long long* acc) {
+// Sums of K values per thread over the workgroup, sum i added into acc[i]
+// (64-bit atomics: exact, so the order of the additions does not matter; null:
+// not wanted).
+template <int K>
+__device__ __forceinline__ void block_add(const uint64_t (&v)[K], uint64_t (*red)[4], unsigned long long* const (&acc)[K]) {
+    static_assert(K <= 4, "red holds four sums per wave");
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    v = wave_sum_u64(v);
-    if (lane == 0) red[wave] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint64_t t = 0;
 #pragma unroll
-        for (int w = 0; w < kBW; ++w) t += red[w];
-        atomicAdd(acc, (unsigned long long)fred64(t));
+    for (int i = 0; i < K; ++i) {
+        const uint64_t w = wave_sum_u64(v[i]);
+        if (lane == 0) red[wave][i] = w;
     }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < K; ++i)
+        if (threadIdx.x == (uint32_t)i && acc[i]) {
+            uint64_t t = 0;
+#pragma unroll
+            for (int w = 0; w < kBW; ++w) t += red[w][i];
+            atomicAdd(acc[i], (unsigned long long)fred64(t));
+        }
     __syncthreads();  // red is reused
 }
 
@@ -65,8 +73,12 @@ struct CheckArgs {
 // ell*ell2: the t x t' lookups of one secondary left side each.  Partial sums go into
 // 64-bit accumulators; the workgroup that finishes last (count.h) reads and
 // clears them and writes the results and the accept bits.
+//
+// Bound by latency: what a workgroup adds up at once is loaded at once, two
+// repetitions (and, of the secondary right sides, two by two) a time, and the
+// last workgroup takes every accumulator with a thread of its own.
 __global__ __launch_bounds__(kBT) void batch_check_kernel(CheckArgs a) {
-    __shared__ uint64_t red[kBW];
+    __shared__ uint64_t red[kBW][4];
     __shared__ uint32_t last;
     const uint32_t bid = blockIdx.x, tid = threadIdx.x;
     const uint32_t Bn = a.B * a.n;
@@ -76,26 +88,44 @@ __global__ __launch_bounds__(kBT) void batch_check_kernel(CheckArgs a) {
         const bool act = k < a.n;
         const uint32_t ks = act ? k : 0u;
         const uint32_t x = act ? a.X[(size_t)b * a.n + ks] : 0u;
-        for (uint32_t q = 0; q < a.ell; ++q)
-            block_add(ffold((uint64_t)a.Ut[(size_t)q * Bn + (size_t)b * a.n + ks] * x), red,
-                      &a.accL[(size_t)q * a.B + b]);
+        for (uint32_t q = 0; q < a.ell; q += 2) {
+            const uint32_t q1 = q + 1 < a.ell ? q + 1 : q;
+            const uint32_t u0 = a.Ut[(size_t)q * Bn + (size_t)b * a.n + ks], u1 = a.Ut[(size_t)q1 * Bn + (size_t)b * a.n + ks];
+            block_add<2>({ffold((uint64_t)u0 * x), ffold((uint64_t)u1 * x)}, red,
+                         {&a.accL[(size_t)q * a.B + b], q1 > q ? &a.accL[(size_t)q1 * a.B + b] : nullptr});
+        }
     } else if (bid < nL + nR) {
         const uint32_t w = bid - nL;
         const uint32_t b = w / a.nbR, i = (w % a.nbR) * kBT + tid;
         const bool act = i < a.m;
         const uint32_t is = act ? i : 0u;
         const uint32_t y = act ? a.Y[(size_t)b * a.m + is] : 0u;
-        for (uint32_t q = 0; q < a.ell; ++q)
-            block_add(ffold((uint64_t)a.R[(size_t)q * a.m + is] * y), red, &a.accR[(size_t)q * a.B + b]);
+        for (uint32_t q = 0; q < a.ell; q += 2) {
+            const uint32_t q1 = q + 1 < a.ell ? q + 1 : q;
+            const uint32_t r0 = a.R[(size_t)q * a.m + is], r1 = a.R[(size_t)q1 * a.m + is];
+            block_add<2>({ffold((uint64_t)r0 * y), ffold((uint64_t)r1 * y)}, red,
+                         {&a.accR[(size_t)q * a.B + b], q1 > q ? &a.accR[(size_t)q1 * a.B + b] : nullptr});
+        }
     } else if (bid < nL + nR + a.nbS) {
         const uint32_t c = (bid - nL - nR) * kBT + tid;
         const bool act = c < Bn;
         const uint32_t cs = act ? c : 0u;
-        for (uint32_t j = 0; j < a.ell2; ++j) {
-            const uint32_t rj = act ? a.Rs[(size_t)j * Bn + cs] : 0u;
-            for (uint32_t q = 0; q < a.ell; ++q)
-                block_add(ffold((uint64_t)rj * a.Ut[(size_t)q * Bn + cs]), red, &a.accS[(size_t)q * a.ell2 + j]);
-        }
+        for (uint32_t j = 0; j < a.ell2; j += 2)
+            for (uint32_t q = 0; q < a.ell; q += 2) {
+                const bool j1 = j + 1 < a.ell2, q1 = q + 1 < a.ell;
+                uint32_t rj[2], uq[2];
+#pragma unroll
+                for (uint32_t i = 0; i < 2; ++i) {
+                    rj[i] = a.Rs[(size_t)(i && j1 ? j + 1 : j) * Bn + cs];
+                    uq[i] = act ? a.Ut[(size_t)(i && q1 ? q + 1 : q) * Bn + cs] : 0u;
+                }
+                unsigned long long* s0 = &a.accS[(size_t)q * a.ell2 + j];
+                block_add<4>({ffold((uint64_t)rj[0] * uq[0]), ffold((uint64_t)rj[1] * uq[0]),
+                              ffold((uint64_t)rj[0] * uq[1]), ffold((uint64_t)rj[1] * uq[1])},
+                             red,
+                             {s0, j1 ? s0 + 1 : nullptr, q1 ? s0 + a.ell2 : nullptr,
+                              q1 && j1 ? s0 + a.ell2 + 1 : nullptr});
+            }
     } else {
         // one (q, j) pair per workgroup; the t x t' lookups kLook per thread
         // and pass, every load of a pass issued before the first use
@@ -123,7 +153,7 @@ __global__ __launch_bounds__(kBT) void batch_check_kernel(CheckArgs a) {
 #pragma unroll
             for (int u = 0; u < kLook; ++u) s += ffold((uint64_t)fmul(w1[u], ent[u]) * w2[u]);
         }
-        block_add(s, red, &a.accA[(size_t)q * a.ell2 + j]);
+        block_add<1>({s}, red, {&a.accA[(size_t)q * a.ell2 + j]});
     }
     // Completion as in the decode/verify kernels: atomics complete (vmcnt 0)
     // before the barrier, the count after it, the last workgroup reads the
@@ -133,10 +163,20 @@ __global__ __launch_bounds__(kBT) void batch_check_kernel(CheckArgs a) {
     if (tid == 0) last = count_last(a.ctrl, a.slots) ? 1u : 0u;
     __syncthreads();
     if (!last) return;
-    // secondary checks (one bit for the batch), then the claims
-    __shared__ uint32_t sec_ok;
+    // secondary checks (one bit for the batch) and, a thread per sum where they
+    // fit, the claims
+    __shared__ uint32_t sec_ok, bad[kBT];
     if (tid == 0) sec_ok = 1u;
+    bad[tid] = 0u;
     __syncthreads();
+    const bool few = a.ell * a.B <= kBT;
+    if (few && tid < a.ell * a.B) {
+        const unsigned long long l = atomicExch(&a.accL[tid], 0ull), r = atomicExch(&a.accR[tid], 0ull);
+        const uint32_t L = fred64(l), Rr = fred64(r);
+        if (a.vL) a.vL[tid] = L;
+        if (a.vR) a.vR[tid] = Rr;
+        if (L != Rr) atomicOr(&bad[tid % a.B], 1u);
+    }
     for (uint32_t o = tid; o < a.ell * a.ell2; o += kBT) {
         const uint32_t L = fred64(atomicExch(&a.accA[o], 0ull));
         const uint32_t Rr = fred64(atomicExch(&a.accS[o], 0ull));
@@ -145,6 +185,10 @@ __global__ __launch_bounds__(kBT) void batch_check_kernel(CheckArgs a) {
         if (L != Rr) atomicAnd(&sec_ok, 0u);
     }
     __syncthreads();
+    if (few) {
+        if (tid < a.B) a.accept[tid] = sec_ok && !bad[tid] ? 1u : 0u;
+        return;
+    }
     for (uint32_t b = tid; b < a.B; b += kBT) {
         uint32_t ok = sec_ok;
         for (uint32_t q = 0; q < a.ell; ++q) {

@@ -70,7 +70,8 @@ def test_keygen_segments(m, n, rx, ry, p):
 # syndromes that join long ones (up to 256 of them, and one more); batch
 # verification with one long and one short code.
 @pytest.mark.parametrize("m,n,rx,ry,B,tx", [(1024, 64, 2, 2, 300, 8), (8192, 300, 3, 3, 40, 20), (4352, 6000, 3, 2, 62, 70),
-                                            (16400, 64, 2, 2, 254, 8), (16400, 64, 2, 2, 260, 8)])
+                                            (16400, 64, 2, 2, 254, 8), (16400, 64, 2, 2, 260, 8),
+                                            (8191, 300, 3, 3, 40, 20), (1100, 8200, 2, 2, 220, 8)])
 @pytest.mark.parametrize("p", [synth.P, synth.P_BABYBEAR])
 def test_prepare_split(m, n, rx, ry, B, tx, p):
     from tests.gpu_util import Instance
@@ -82,7 +83,7 @@ def test_prepare_split(m, n, rx, ry, B, tx, p):
     zero = np.zeros((B, n), dtype=np.uint32)
     Mx = oracle.encode(t.cx, zero, t.exi, t.exv, p=p)
     assert np.array_equal(host(prep.Mx), Mx)
-    assert np.array_equal(host(prep.My), oracle.server_eval(t.W, Mx, p=p))
+    assert np.array_equal(host(prep.My), oracle.server_eval(t.W, Mx, p=p, nthreads=oracle.threads()))
     R = oracle.encode(t.cy, np.zeros((2, m), dtype=np.uint32), t.eyi, t.eyv, p=p)
     assert np.array_equal(host(prep.R), R)
     assert np.array_equal(host(prep.U), oracle.server_eval(np.ascontiguousarray(t.W.T), R, p=p))
@@ -139,3 +140,30 @@ def test_many_k_ranges(m, n, B, p):
     for dW in (dev(W), mvk.pack_weights(dev(W))):
         for _ in range(2):
             assert np.array_equal(host(mvk.server_eval(dW, dev(X), p=p)), want)
+
+
+# Batch verification with one long and one short code (both by segments), odd
+# numbers of repetitions, and more sums than threads in the last workgroup.
+@pytest.mark.parametrize("m,n,B,ell,ell2", [(300, 2100, 4, 2, 2), (5500, 70, 3, 3, 1), (300, 2100, 4, 1, 5), (20, 30, 86, 3, 4)])
+def test_batch_long_and_short_code(m, n, B, ell, ell2):
+    cy, c2 = synth.raa_code(620 + m, m, 3), synth.raa_code(621 + n, B * n, 2)
+    from tests.gpu_util import code
+    Ws = [synth.weights(622 + b, m, n) for b in range(B)]
+    X = synth.field_uniform(630, (B, n))
+    ei, ev = synth.sparse(631, ell, cy["N"], 31)
+    e2i, e2v = synth.sparse(632, ell2, c2["N"], 31)
+    one = synth.raa_code(633, n, 2)
+    Qs = [mvk.keygen(mvk.Key.allocate(m, n, code(one), code(cy)), dev(W)).Q for W in Ws]
+    QtT, Qaux = mvk.batch_preprocess(Qs, code(c2))
+    Y = np.concatenate([oracle.server_eval(W, X[b:b + 1]) for b, W in enumerate(Ws)])
+    Y[B - 1, m - 1] = (int(Y[B - 1, m - 1]) + 1) % synth.P
+    ut = mvk.batch_project(QtT, n, dev(ei), dev(ev))
+    out = [torch.empty((ell, k), dtype=torch.int32, device="cuda") for k in (B, B, ell2, ell2)]
+    acc = mvk.batch_verify(code(cy), code(c2), Qaux, dev(X), dev(Y), dev(ei), dev(ev), ut, dev(e2i), dev(e2v),
+                           vL=out[0], vR=out[1], sL=out[2], sR=out[3])[0]
+    hQ = [host(Q) for Q in Qs]
+    oacc, _, *want = oracle.batch_verify(cy, c2, oracle.batch_aux(hQ, c2), X, Y, ei, ev,
+                                         oracle.batch_project(hQ, ei, ev), e2i, e2v)
+    assert host(acc).tolist() == oacc.astype(np.uint32).tolist() == [1] * (B - 1) + [0]
+    for got, w in zip(out, want):
+        assert np.array_equal(host(got), w)
