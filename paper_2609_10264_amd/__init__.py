@@ -36,10 +36,11 @@ def library_path(p: int = P) -> str:
     return _lib.LIB_PATHS[p]
 
 
-def _stream(stream) -> ctypes.c_void_p:
+def _stream(stream) -> int:
+    # (the raw handle: building a Stream object takes longer than the call it is for)
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _dev(t: torch.Tensor, dtype: torch.dtype, shape: tuple | None, name: str) -> int:
@@ -49,7 +50,7 @@ def _dev(t: torch.Tensor, dtype: torch.dtype, shape: tuple | None, name: str) ->
         raise TypeError(f"{name} must have dtype {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape and tuple(t.shape) != tuple(shape):
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
     return t.data_ptr()
 
