@@ -16,6 +16,7 @@
 #include "masks.h"
 #include "mvk_internal.h"
 #include "syn_block.h"
+#include "syn_seg.h"
 
 namespace mvk {
 
@@ -322,12 +323,11 @@ __global__ __launch_bounds__(kPrepThreads) void client_prepare_kernel(PrepArgs a
 // the kernels of other streams instead of taking whole ones.  The syndromes
 // then run before, in client_prepare_kernel launched with their workgroups
 // only.  SIG as in client_prepare_kernel.
+constexpr size_t gather_part_of(bool vec, bool wide) { return wide ? gather_part_wide() : gather_part(vec); }
 template <bool SIG, bool VEC, bool WIDE>
-__global__ __launch_bounds__(kQuarter) void client_gather_kernel(PrepArgs a) {
+__device__ __forceinline__ void gather_role(const PrepArgs& a, uint32_t item, uint64_t* part) {
     static_assert(!WIDE || VEC, "wide items read 16 bytes per lane and piece");
-    __shared__ __align__(16) uint64_t part[WIDE ? gather_part_wide() : gather_part(VEC)];
     constexpr uint32_t cols = WIDE ? kWideCols : gather_cols(VEC);
-    uint32_t item = blockIdx.x;
     uint32_t g = 0;
     while (g < a.G && item >= a.it_end[g]) ++g;
     if (g < a.G) {
@@ -357,6 +357,12 @@ __global__ __launch_bounds__(kQuarter) void client_gather_kernel(PrepArgs a) {
         else
             gather_item<SIG, VEC>(nullptr, 0u, 1u, nullptr, nullptr, 0u, nullptr, 0u, false, part);
     }
+}
+
+template <bool SIG, bool VEC, bool WIDE>
+__global__ __launch_bounds__(kQuarter) void client_gather_kernel(PrepArgs a) {
+    __shared__ __align__(16) uint64_t part[gather_part_of(VEC, WIDE)];
+    gather_role<SIG, VEC, WIDE>(a, blockIdx.x, part);
     if constexpr (SIG) {
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
@@ -366,6 +372,36 @@ __global__ __launch_bounds__(kQuarter) void client_gather_kernel(PrepArgs a) {
     }
 }
 
+
+// The gathers beside the second pass of the syndromes by segments.  The gathers
+// are bound by HBM and need no syndrome, and a pass that the chip holds at once
+// (one stripe per workgroup) is bound by the latency of its look-back: a decoder
+// layer with 8 columns takes 134.0 us against 139.0 with two launches.  A pass
+// of four stripes is bound by the L2's rate of scattered words instead, and
+// loses more beside the gathers than they gain (28672 x 8192, 64 columns: 191 us
+// against 23 + 156).  Groups of eight workgroups (one per XCD: the pass places
+// its vectors by XCD) alternate in proportion, so that both run from the start
+// to the end: pass_groups of `groups` belong to the pass.  (A workgroup of the
+// pass waits only for workgroups that already run, whatever the order.)
+template <bool VEC, bool WIDE>
+__global__ __launch_bounds__(kQuarter) void client_gather_pass_kernel(PrepArgs a, synseg::SegArgs sa, uint32_t gx,
+                                                                      uint32_t rows, uint32_t items,
+                                                                      uint32_t pass_groups, uint32_t groups) {
+    constexpr size_t kPart = gather_part_of(VEC, WIDE) * sizeof(uint64_t), kSeg = sizeof(synseg::SegLds<1>);
+    __shared__ __align__(16) uint8_t lds[kPart > kSeg ? kPart : kSeg];
+    static_assert(kQuarter == synseg::kSegThreads, "one workgroup shape for both roles");
+    const uint32_t g = blockIdx.x / synseg::kXcds, x = blockIdx.x % synseg::kXcds;
+    const uint32_t before = (uint32_t)((uint64_t)g * pass_groups / groups);  // groups of the pass before this one
+    if ((uint32_t)((uint64_t)(g + 1) * pass_groups / groups) > before) {
+        const uint32_t w = before * synseg::kXcds + x;
+        if (w < gx * rows)
+            synseg::seg_second_scatter<1>(sa, w % gx, w / gx, gx, *reinterpret_cast<synseg::SegLds<1>*>(lds));
+    } else {
+        const uint32_t item = (g - before) * synseg::kXcds + x;
+        if (item < items) gather_role<false, VEC, WIDE>(a, item, reinterpret_cast<uint64_t*>(lds));
+    }
+}
+static_assert(sizeof(PrepArgs) + sizeof(synseg::SegArgs) + 64 <= 4096, "the arguments fit a launch");
 
 // out[v][i] = sum_s val[v*t + s] * M[idx[v*t + s], i] for `count` sparse
 // vectors v (M: nrows x ld): nb = ceil(ld / gather_cols(VEC)) items per
@@ -573,8 +609,20 @@ hipError_t launch_client_prepare_multi(const PrepInputDesc* ins, uint32_t NI, co
     // syndromes by segments run first, all of them in one sequence of launches
     SynSet sets[2 * kMaxPrep];
     const uint32_t S = seg_sets(ins, NI, probs, G, pl.join, sets);
+    // the second pass goes with the gathers (client_gather_pass_kernel) where
+    // these have their own launch and nobody waits for a flag, which the last
+    // gather would set
+    synseg::SegArgs sa{};
+    synseg::SegShape sh{};
+    bool beside = false;
     if (S) {
-        const hipError_t e = launch_syn_sets(sets, S, scratch, scratch_bytes, s);
+        if (!synseg::seg_args(sets, S, scratch, scratch_bytes, &sa)) return hipErrorInvalidValue;
+        sh = synseg::seg_shape(sa);
+        const uint64_t all = (uint64_t)sh.gx * sh.rows + pl.grid;
+        beside = pl.split && !(done && ndone) && sh.stripes == 1 && sh.rows && sh.rows <= 65535u && pl.grid &&
+                 all < 0x7fffff00u;
+        const hipError_t e = beside ? synseg::launch_seg_first(sa, sh, s)
+                                    : launch_syn_sets(sets, S, scratch, scratch_bytes, s);
         if (e != hipSuccess) return e;
     }
     if (pl.grid == 0) return hipSuccess;
@@ -599,6 +647,20 @@ hipError_t launch_client_prepare_multi(const PrepInputDesc* ins, uint32_t NI, co
     for (uint32_t f = 0; f < a.ndone; ++f) a.done[f] = done[f];
     a.done_value = done_value;
     const bool sig = a.ndone > 0;
+    if (beside) {
+        const uint32_t pg = ceil_div(sh.gx * sh.rows, synseg::kXcds);
+        const uint32_t groups = pg + ceil_div((uint32_t)pl.grid, synseg::kXcds);
+        const dim3 bgrid(groups * synseg::kXcds), bblock(kQuarter);
+#define MVK_BESIDE(V, W)                                                                                             \
+    hipLaunchKernelGGL((client_gather_pass_kernel<V, W>), bgrid, bblock, 0, s, a, sa, sh.gx, sh.rows, (uint32_t)pl.grid, \
+                       pg, groups)
+        if (pl.wide) MVK_BESIDE(true, true);
+        else if (pl.vec) MVK_BESIDE(true, false);
+        else MVK_BESIDE(false, false);
+#undef MVK_BESIDE
+        const hipError_t e = hipGetLastError();
+        return e == hipSuccess ? synseg::launch_seg_last(sa, sh, s) : e;
+    }
     if (pl.split) {
         const dim3 ggrid((uint32_t)pl.grid), gblock(kQuarter);
         if (sig) {

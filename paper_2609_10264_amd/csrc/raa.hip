@@ -449,51 +449,11 @@ __global__ __launch_bounds__(kSynThreads) void syn_wg(uint32_t k, uint32_t r, co
 // look-back state: per vector one ticket word and one status word per segment
 // (bit 32 set once the segment's sum, in the low 31 bits, is published).
 // ---------------------------------------------------------------------------
-// Several syndromes of long blocks share each of the three launches: set i is
-// count vectors over its own code, with its own work region (count x 2N words
-// and the look-back state).  grid.y runs over the vectors of all sets, grid.x
-// over the segments (p1, p2) or the fold chunks (p3) of the longest; the
-// workgroups past a shorter set's end return at once (before p2's ticket).
-struct SegArgs {
-    uint32_t S;
-    uint32_t by_xcd;             // vectors [0, by_xcd) are placed by XCD (seg_place)
-    uint32_t vend[kMaxSynSets];  // vectors of sets < i + 1
-    SegSet set[kMaxSynSets];
-};
-
-// Which vector and segment a workgroup of the (segments, vectors) grid takes.
-// Workgroups go to the 8 XCDs in turn by their linear index, and each XCD has
-// its own L2.  The scatters write 4-byte words all over a vector's work array:
-// with a vector's segments on every XCD each L2 held a few words of every line,
-// and the lines went to memory in pieces.  Vectors below by_xcd (a multiple of
-// 8) are taken eight at a time, one per XCD, so that one L2 collects whole
-// lines; the vectors left over keep the plain order, which spreads each over
-// the chip.
-constexpr uint32_t kXcds = 8;
-__device__ __forceinline__ void seg_place(const SegArgs& a, uint32_t* vy, uint32_t* seg) {
-    if (blockIdx.y >= a.by_xcd) {
-        *vy = blockIdx.y;
-        *seg = blockIdx.x;
-        return;
-    }
-    const uint32_t within = blockIdx.x + gridDim.x * (blockIdx.y % kXcds);  // of eight vectors' workgroups
-    *vy = blockIdx.y - blockIdx.y % kXcds + within % kXcds;
-    *seg = within / kXcds;
-}
-
-// The set of global vector vy (grid.y) and the vector's index within it.
-__device__ __forceinline__ const SegSet& seg_set(const SegArgs& a, uint32_t vy, uint32_t* c) {
-    uint32_t i = 0;
-    while (vy >= a.vend[i]) ++i;
-    *c = vy - (i ? a.vend[i - 1] : 0u);
-    return a.set[i];
-}
-
 template <bool SPARSE, int NS>
 __global__ __launch_bounds__(kSegThreads) void syn_p1(const SegArgs a) {
     __shared__ SegLds<NS> lds;
     uint32_t c, vy, sg;
-    seg_place(a, &vy, &sg);
+    seg_place(a, blockIdx.x, blockIdx.y, gridDim.x, &vy, &sg);
     if (vy >= a.vend[a.S - 1]) return;
     const SegSet& S = seg_set(a, vy, &c);
     if (sg >= seg_count<NS>(S.k * S.r)) return;
@@ -503,28 +463,12 @@ __global__ __launch_bounds__(kSegThreads) void syn_p1(const SegArgs a) {
 template <int NS>
 __global__ __launch_bounds__(kSegThreads) void syn_p2(const SegArgs a) {
     __shared__ SegLds<NS> lds;
-    uint32_t c, vy, place;
-    seg_place(a, &vy, &place);
-    if (vy >= a.vend[a.S - 1]) return;
-    const SegSet& S = seg_set(a, vy, &c);
-    const uint32_t N = S.k * S.r;
-    if (place >= seg_count<NS>(N)) return;  // (uniform: no ticket taken)
-    uint32_t x[NS][kSegPer], p1[NS][kSegPer], w1[NS][kSegPer];
-    const uint32_t sg = seg_second_load<NS>(S, c, lds, x, p1, w1);
-    seg_second_scan<NS>(S, c, sg, lds, x);
-    const uint32_t j0 = sg * NS * kSegLen + threadIdx.x * kSegPer;
-    uint32_t* dbuf = S.work + (size_t)c * 2 * N + N;
-#pragma unroll
-    for (int v = 0; v < NS; ++v)
-#pragma unroll
-        for (int e = 0; e < kSegPer; ++e)
-            if (j0 + v * kSegLen + e < N)
-                dbuf[p1[v][e] < N ? p1[v][e] : N - 1] = fmul(w1[v][e], x[v][e]);  // V1, then Pi1 scatter
+    seg_second_scatter<NS>(a, blockIdx.x, blockIdx.y, gridDim.x, lds);
 }
 
 __global__ __launch_bounds__(256) void syn_p3(const SegArgs a) {
     uint32_t c, vy, chunk;
-    seg_place(a, &vy, &chunk);
+    seg_place(a, blockIdx.x, blockIdx.y, gridDim.x, &vy, &chunk);
     if (vy >= a.vend[a.S - 1]) return;
     const SegSet& S = seg_set(a, vy, &c);
     const uint32_t N = S.k * S.r;
@@ -537,42 +481,31 @@ __global__ __launch_bounds__(256) void syn_p3(const SegArgs a) {
     S.out[(size_t)c * S.k + i] = s;
 }
 
+template <bool SPARSE>
+hipError_t launch_p1(const SegArgs& a, const SegShape& h, hipStream_t s) {
+    const dim3 grid(h.gx, h.rows);
+    if (h.stripes == 4)
+        hipLaunchKernelGGL((syn_p1<SPARSE, 4>), grid, dim3(kSegThreads), 0, s, a);
+    else
+        hipLaunchKernelGGL((syn_p1<SPARSE, 1>), grid, dim3(kSegThreads), 0, s, a);
+    return hipGetLastError();
+}
+
 // The three launches over sets of one input kind (sparse or dense).
 template <bool SPARSE>
 hipError_t launch_seg_sets(SegArgs a, hipStream_t s) {
-    uint32_t maxk = 0, maxN = 0;
-    uint64_t segs = 0;  // workgroups with one stripe each
-    for (uint32_t i = 0; i < a.S; ++i) {
-        const uint32_t N = a.set[i].k * a.set[i].r;
-        segs += (uint64_t)seg_count<1>(N) * a.set[i].count;
-        maxN = N > maxN ? N : maxN;
-        maxk = a.set[i].k > maxk ? a.set[i].k : maxk;
-    }
-    const uint32_t nv = a.S ? a.vend[a.S - 1] : 0u;
-    if (nv == 0) return hipSuccess;
-    if (nv > 65535u) return hipErrorInvalidValue;
-    // placed by XCD: whole eights, and a rest of six or more (its empty places
-    // return at once; fewer vectors would leave XCDs idle)
-    a.by_xcd = (nv + 2) / kXcds * kXcds;
-    if (a.by_xcd > 65535u) a.by_xcd = nv / kXcds * kXcds;
-    const uint32_t rows = nv > a.by_xcd ? nv : a.by_xcd;
-    // four stripes per workgroup where one each would be more workgroups than
-    // the chip holds at once (eight per compute unit)
-    hipError_t e;
-    if (segs > 2048) {
-        const dim3 gseg(seg_count<4>(maxN), rows);
-        hipLaunchKernelGGL((syn_p1<SPARSE, 4>), gseg, dim3(kSegThreads), 0, s, a);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL((syn_p2<4>), gseg, dim3(kSegThreads), 0, s, a);
-    } else {
-        const dim3 gseg(seg_count<1>(maxN), rows);
-        hipLaunchKernelGGL((syn_p1<SPARSE, 1>), gseg, dim3(kSegThreads), 0, s, a);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL((syn_p2<1>), gseg, dim3(kSegThreads), 0, s, a);
-    }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(syn_p3, dim3(ceil_div(maxk, 256u), rows), dim3(256), 0, s, a);
-    return hipGetLastError();
+    const SegShape h = seg_shape(a);
+    if (h.rows == 0) return hipSuccess;
+    if (h.rows > 65535u) return hipErrorInvalidValue;
+    hipError_t e = launch_p1<SPARSE>(a, h, s);
+    if (e != hipSuccess) return e;
+    const dim3 grid(h.gx, h.rows);
+    if (h.stripes == 4)
+        hipLaunchKernelGGL((syn_p2<4>), grid, dim3(kSegThreads), 0, s, a);
+    else
+        hipLaunchKernelGGL((syn_p2<1>), grid, dim3(kSegThreads), 0, s, a);
+    e = hipGetLastError();
+    return e == hipSuccess ? launch_seg_last(a, h, s) : e;
 }
 
 template <bool SPARSE>
@@ -767,10 +700,44 @@ size_t syn_sets_scratch_bytes(const SynSet* sets, uint32_t S) {
     return b;
 }
 
-hipError_t launch_syn_sets(const SynSet* sets, uint32_t S, uint32_t* scratch, size_t scratch_bytes, hipStream_t s) {
-    if (S > kMaxSynSets) return hipErrorInvalidValue;
+namespace synseg {
+SegShape seg_shape(SegArgs& a) {
+    SegShape h{0, 0, 1, 0};
+    uint32_t maxN = 0;
+    uint64_t segs = 0;  // workgroups with one stripe each
+    for (uint32_t i = 0; i < a.S; ++i) {
+        const uint32_t N = a.set[i].k * a.set[i].r;
+        segs += (uint64_t)seg_count<1>(N) * a.set[i].count;
+        maxN = N > maxN ? N : maxN;
+        h.maxk = a.set[i].k > h.maxk ? a.set[i].k : h.maxk;
+    }
+    const uint32_t nv = a.S ? a.vend[a.S - 1] : 0u;
+    // placed by XCD: whole eights, and a rest of six or more (its empty places
+    // return at once; fewer vectors would leave XCDs idle)
+    a.by_xcd = (nv + 2) / kXcds * kXcds;
+    if (a.by_xcd > 65535u) a.by_xcd = nv / kXcds * kXcds;
+    h.rows = nv > a.by_xcd ? nv : a.by_xcd;
+    // four stripes per workgroup where one each would be more workgroups than
+    // the chip holds at once (eight per compute unit)
+    h.stripes = segs > 2048 ? 4u : 1u;
+    h.gx = h.stripes == 4 ? seg_count<4>(maxN) : seg_count<1>(maxN);
+    return h;
+}
+
+hipError_t launch_seg_first(const SegArgs& a, const SegShape& h, hipStream_t s) {
+    return launch_p1<true>(a, h, s);
+}
+
+hipError_t launch_seg_last(const SegArgs& a, const SegShape& h, hipStream_t s) {
+    hipLaunchKernelGGL(syn_p3, dim3(ceil_div(h.maxk, 256u), h.rows), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+}  // namespace synseg
+
+bool synseg::seg_args(const SynSet* sets, uint32_t S, uint32_t* scratch, size_t scratch_bytes, SegArgs* out) {
+    if (S > kMaxSynSets) return false;
     // the sets' work regions lie one after another: the scratch must hold them all
-    if (syn_sets_scratch_bytes(sets, S) > scratch_bytes) return hipErrorInvalidValue;
+    if (syn_sets_scratch_bytes(sets, S) > scratch_bytes) return false;
     SegArgs a{};
     uint32_t nv = 0;
     char* w = reinterpret_cast<char*>(scratch);
@@ -784,7 +751,13 @@ hipError_t launch_syn_sets(const SynSet* sets, uint32_t S, uint32_t* scratch, si
         a.vend[a.S++] = nv;
         w += (syn_seg_bytes(d.count, N) + 255) & ~(size_t)255;
     }
-    return launch_seg_sets<true>(a, s);
+    *out = a;
+    return nv <= 65535u;
+}
+
+hipError_t launch_syn_sets(const SynSet* sets, uint32_t S, uint32_t* scratch, size_t scratch_bytes, hipStream_t s) {
+    SegArgs a;
+    return seg_args(sets, S, scratch, scratch_bytes, &a) ? launch_seg_sets<true>(a, s) : hipErrorInvalidValue;
 }
 
 hipError_t launch_syn_dense(const mvk_code& c, const uint32_t* v, uint32_t count, uint32_t* scratch, uint32_t* out,

@@ -98,6 +98,60 @@ struct SegSet {
     uint32_t* work;
     uint32_t k, r, t, count;
 };
+// Several syndromes of long blocks share each of the three launches: set i is
+// count vectors over its own code, with its own work region (count x 2N words
+// and the look-back state).  grid.y runs over the vectors of all sets, grid.x
+// over the segments (p1, p2) or the fold chunks (p3) of the longest; the
+// workgroups past a shorter set's end return at once (before p2's ticket).
+struct SegArgs {
+    uint32_t S;
+    uint32_t by_xcd;             // vectors [0, by_xcd) are placed by XCD (seg_place)
+    uint32_t vend[kMaxSynSets];  // vectors of sets < i + 1
+    SegSet set[kMaxSynSets];
+};
+
+// Which vector and segment a workgroup of the (segments, vectors) grid takes.
+// Workgroups go to the 8 XCDs in turn by their linear index, and each XCD has
+// its own L2.  The scatters write 4-byte words all over a vector's work array:
+// with a vector's segments on every XCD each L2 held a few words of every line,
+// and the lines went to memory in pieces.  Vectors below by_xcd (a multiple of
+// 8) are taken eight at a time, one per XCD, so that one L2 collects whole
+// lines; the vectors left over keep the plain order, which spreads each over
+// the chip.
+constexpr uint32_t kXcds = 8;
+__device__ __forceinline__ void seg_place(const SegArgs& a, uint32_t bx, uint32_t by, uint32_t gx, uint32_t* vy,
+                                          uint32_t* seg) {
+    if (by >= a.by_xcd) {
+        *vy = by;
+        *seg = bx;
+        return;
+    }
+    const uint32_t within = bx + gx * (by % kXcds);  // of eight vectors' workgroups
+    *vy = by - by % kXcds + within % kXcds;
+    *seg = within / kXcds;
+}
+
+// The set of global vector vy (grid.y) and the vector's index within it.
+__device__ __forceinline__ const SegSet& seg_set(const SegArgs& a, uint32_t vy, uint32_t* c) {
+    uint32_t i = 0;
+    while (vy >= a.vend[i]) ++i;
+    *c = vy - (i ? a.vend[i - 1] : 0u);
+    return a.set[i];
+}
+
+// The grid of the passes over a set of sets: gx workgroups (segments) for each of
+// `rows` vectors (some of them empty places), `stripes` per workgroup.
+struct SegShape {
+    uint32_t gx, rows, stripes, maxk;
+};
+// The arguments for S sparse sets with their work regions in scratch (false:
+// too little of it, or too many vectors); the shape (sets a.by_xcd); the first
+// pass, the fold.  The second pass is seg_second_scatter.
+bool seg_args(const SynSet* sets, uint32_t S, uint32_t* scratch, size_t scratch_bytes, SegArgs* out);
+SegShape seg_shape(SegArgs& a);
+hipError_t launch_seg_first(const SegArgs& a, const SegShape& h, hipStream_t s);
+hipError_t launch_seg_last(const SegArgs& a, const SegShape& h, hipStream_t s);
+
 // Segments of a block of N positions.
 template <int NS>
 __host__ __device__ inline uint32_t seg_count(uint32_t N) {
@@ -246,6 +300,29 @@ __device__ __forceinline__ void seg_second_scan(const SegSet& S, uint32_t c, uin
     }
     __syncthreads();
     seg_suffix_scan<NS>(x, lds.sh_carry, lds.wsum);  // A
+}
+
+// p2 of workgroup (bx, by) of a grid gx wide.
+template <int NS>
+__device__ __forceinline__ void seg_second_scatter(const SegArgs& a, uint32_t bx, uint32_t by, uint32_t gx,
+                                                   SegLds<NS>& lds) {
+    uint32_t c, vy, place;
+    seg_place(a, bx, by, gx, &vy, &place);
+    if (vy >= a.vend[a.S - 1]) return;
+    const SegSet& S = seg_set(a, vy, &c);
+    const uint32_t N = S.k * S.r;
+    if (place >= seg_count<NS>(N)) return;  // (uniform: no ticket taken)
+    uint32_t x[NS][kSegPer], p1[NS][kSegPer], w1[NS][kSegPer];
+    const uint32_t sg = seg_second_load<NS>(S, c, lds, x, p1, w1);
+    seg_second_scan<NS>(S, c, sg, lds, x);
+    const uint32_t j0 = sg * NS * kSegLen + threadIdx.x * kSegPer;
+    uint32_t* dbuf = S.work + (size_t)c * 2 * N + N;
+#pragma unroll
+    for (int v = 0; v < NS; ++v)
+#pragma unroll
+        for (int e = 0; e < kSegPer; ++e)
+            if (j0 + v * kSegLen + e < N)
+                dbuf[p1[v][e] < N ? p1[v][e] : N - 1] = fmul(w1[v][e], x[v][e]);  // V1, then Pi1 scatter
 }
 
 }  // namespace synseg

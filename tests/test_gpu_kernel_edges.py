@@ -67,8 +67,9 @@ def test_keygen_segments(m, n, rx, ry, p):
 
 # Preparations whose gathers take their own launch: many columns of a short
 # matrix, where items of 1024 columns would no longer need that launch; short
-# syndromes that join long ones (up to 256 of them, and one more); batch
-# verification with one long and one short code.
+# syndromes that join long ones (up to 256 of them, and one more); the gathers
+# beside the second pass of long ones (one stripe per workgroup), by items of 64,
+# 256 and 1024 columns; four stripes.
 @pytest.mark.parametrize("m,n,rx,ry,B,tx", [(1024, 64, 2, 2, 300, 8), (8192, 300, 3, 3, 40, 20), (4352, 6000, 3, 2, 62, 70),
                                             (16400, 64, 2, 2, 254, 8), (16400, 64, 2, 2, 260, 8),
                                             (8191, 300, 3, 3, 40, 20), (1100, 8200, 2, 2, 220, 8)])
