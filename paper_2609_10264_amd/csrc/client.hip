@@ -496,17 +496,23 @@ __global__ __launch_bounds__(kFusedThreads) void decode_verify_syn(
 // so a workgroup that holds z at some positions adds its share of v_R itself:
 // no scatter by Pi1, no fold, and nobody waits for a whole r_q.  The price is r
 // times as many products with Yhat, gathered, which is why this is for few
-// columns (kDotMaxB).
+// columns.  Short blocks, where it takes the place of a whole syndrome: up to 16
+// columns (two repetitions, 4096 x 4096, r = 3: 14.6 us against 23.9 with 8
+// columns, 18.6 against 25.0 with 16), up to 8 where the syndrome is of 4096
+// positions at most (256 x 256, r = 2: 8.4 us against 10.1 with 8, 11.2 against
+// 10.2 with 16).  Long ones: up to 4 columns and 8 sums (16384 x 16384, r = 8:
+// 24.4 us against 36.3 with 2 columns, 31.7 with 4; with 8 it takes 42 where the
+// syndromes and decode_verify_fused take 37).
 //
-// Adds the sums over the workgroup of x[b] (b < kDotMaxB; columns < B) to
+// Adds the sums over the workgroup of x[b] (b < MB; columns < B) to
 // accumulator (q, b, sub).  NW waves.
-constexpr uint32_t kDotMaxB = 8;
-template <int NW>
-__device__ __forceinline__ void dot_add(const uint64_t (&x)[kDotMaxB], uint32_t B, uint32_t q, uint32_t sub,
-                                        unsigned long long* accR, uint32_t nsub, uint64_t (*red)[kDotMaxB]) {
+constexpr uint32_t kDotMaxB = 16, kDotMaxBSmall = 8, kDotSmall = 4096, kDotMaxBLong = 4, kDotMaxSumsLong = 8;
+template <int NW, int MB>
+__device__ __forceinline__ void dot_add(const uint64_t (&x)[MB], uint32_t B, uint32_t q, uint32_t sub,
+                                        unsigned long long* accR, uint32_t nsub, uint64_t (*red)[MB]) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-    for (uint32_t b = 0; b < kDotMaxB; ++b) {
+    for (uint32_t b = 0; b < MB; ++b) {
         if (b >= B) break;
         const uint64_t w = wave_sum_u64(x[b]);
         if (lane == 0) red[wave][b] = w;
@@ -561,19 +567,20 @@ struct TermSums {
 // products per workgroup (1.2 us of one CU at N = 12288) and takes the place
 // of a scan and two scatters of the whole block by one CU (about 10 us).
 constexpr uint32_t kSortMax = 64;
+template <int MB>
 struct DotLds {
     uint32_t y[kFusedThreads];
     uint64_t carry[kFusedGroups];
     uint32_t wsum[kFusedGroups];
-    uint64_t red[kFusedGroups][kDotMaxB];
+    uint64_t red[kFusedGroups][MB];
 };
-template <int U>
+template <int U, int MB>
 __device__ __forceinline__ void syn_dot_part(uint32_t q, uint32_t seg, uint32_t m, uint32_t r, uint32_t N,
                                              const uint32_t* __restrict__ pi1, const uint32_t* __restrict__ pi2,
                                              const uint32_t* __restrict__ v1, const uint32_t* __restrict__ v2,
                                              const uint32_t* __restrict__ ey_idx, const uint32_t* __restrict__ ey_val,
                                              uint32_t ty, const uint32_t* __restrict__ Yhat, uint32_t B,
-                                             unsigned long long* accR, uint32_t nsub, DotLds& lds) {
+                                             unsigned long long* accR, uint32_t nsub, DotLds<MB>& lds) {
     constexpr uint32_t T = kFusedThreads;
     const uint32_t tid = threadIdx.x, lane = tid & 63;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -597,9 +604,9 @@ __device__ __forceinline__ void syn_dot_part(uint32_t q, uint32_t seg, uint32_t 
     S.sort(sj, sv, ty, N);
     lds.y[tid] = 0u;
     const uint32_t row = (p1 < N ? p1 : N - 1) / r;  // < m
-    uint32_t yv[kDotMaxB];
+    uint32_t yv[MB];
 #pragma unroll
-    for (uint32_t b = 0; b < kDotMaxB; ++b) yv[b] = b < B ? Yhat[(size_t)b * m + row] : 0u;
+    for (uint32_t b = 0; b < MB; ++b) yv[b] = b < B ? Yhat[(size_t)b * m + row] : 0u;
     __syncthreads();
     uint64_t carry = 0;
 #pragma unroll
@@ -625,16 +632,16 @@ __device__ __forceinline__ void syn_dot_part(uint32_t q, uint32_t seg, uint32_t 
     for (uint32_t w = 0; w < kFusedGroups; ++w) after += lds.carry[w] + (w > wave ? lds.wsum[w] : 0u);
     const uint32_t z = fadd(fadd(x, fsub(lds.wsum[wave], incl)), fred64(after));
     const uint32_t c = in ? fmul(w1, z) : 0u;
-    uint64_t t[kDotMaxB];
+    uint64_t t[MB];
 #pragma unroll
-    for (uint32_t b = 0; b < kDotMaxB; ++b) t[b] = ffold((uint64_t)c * yv[b]);
-    dot_add<kFusedGroups>(t, B, q, seg % nsub, accR, nsub, lds.red);
+    for (uint32_t b = 0; b < MB; ++b) t[b] = ffold((uint64_t)c * yv[b]);
+    dot_add<kFusedGroups, MB>(t, B, q, seg % nsub, accR, nsub, lds.red);
 }
 
 // One launch for blocks of up to kFusedThreads * U positions: workgroups
 // [0, ell nseg) add up v_R (syn_dot_part), the next nblkL v_L (verify role),
 // the rest decrypt (Y only; they add nothing and do not count).
-template <int U>
+template <int U, int MB>
 __global__ __launch_bounds__(kFusedThreads) void decode_verify_dot(
     const uint32_t* __restrict__ PT, const uint32_t* __restrict__ Q, uint32_t m, uint32_t n, uint32_t Nx,
     uint32_t Ny, const uint32_t* __restrict__ Xhat, const uint32_t* __restrict__ Yhat, uint32_t B,
@@ -647,7 +654,7 @@ __global__ __launch_bounds__(kFusedThreads) void decode_verify_dot(
     uint32_t* __restrict__ accept) {
     constexpr size_t kWords = kGatherWords > kDecodeWords ? kGatherWords : kDecodeWords;
     __shared__ __align__(16) uint32_t lds[kWords];
-    static_assert(sizeof(DotLds) <= sizeof(lds), "the roles share the LDS");
+    static_assert(sizeof(DotLds<MB>) <= sizeof(lds), "the roles share the LDS");
     __shared__ uint32_t last;
     const uint32_t bid = blockIdx.x, ndot = ell * nseg, counted = ndot + nblkL;
     if (bid >= counted) {
@@ -658,8 +665,8 @@ __global__ __launch_bounds__(kFusedThreads) void decode_verify_dot(
         return;
     }
     if (bid < ndot)
-        syn_dot_part<U>(bid / nseg, bid % nseg, m, cyr, Ny, pi1, pi2, v1, v2, ey_idx, ey_val, ty, Yhat, B, accR, nsub,
-                        *reinterpret_cast<DotLds*>(lds));
+        syn_dot_part<U, MB>(bid / nseg, bid % nseg, m, cyr, Ny, pi1, pi2, v1, v2, ey_idx, ey_val, ty, Yhat, B, accR, nsub,
+                        *reinterpret_cast<DotLds<MB>*>(lds));
     else
         verify_part<kFusedGroups>(Q, n, Ny, Xhat, B, ey_idx, ey_val, ty, ell, accL, nsub, bid - ndot,
                                   reinterpret_cast<uint64_t (*)[kCols]>(lds),
@@ -699,30 +706,30 @@ __global__ __launch_bounds__(synseg::kSegThreads) void decode_verify_long2(
     const synseg::SegSet S, uint32_t m, const uint32_t* __restrict__ Yhat, uint32_t B, unsigned long long* accL,
     unsigned long long* accR, uint32_t nsub, uint32_t nseg, uint32_t* ctrl, uint32_t slots,
     uint32_t* __restrict__ vL, uint32_t* __restrict__ vR, uint32_t* __restrict__ accept) {
-    constexpr int P = synseg::kSegPer;
+    constexpr int P = synseg::kSegPer, MB = kDotMaxBLong;
     __shared__ synseg::SegLds<1> lds;
-    __shared__ uint64_t red[synseg::kSegThreads / 64][kDotMaxB];
+    __shared__ uint64_t red[synseg::kSegThreads / 64][MB];
     __shared__ uint32_t last;
     const uint32_t q = blockIdx.x / nseg, N = S.k * S.r;
     uint32_t x[1][P], p1[1][P], w1[1][P];
     const uint32_t sg = synseg::seg_second_load<1>(S, q, lds, x, p1, w1);
-    uint32_t yv[P][kDotMaxB];
+    uint32_t yv[P][MB];
 #pragma unroll
     for (int e = 0; e < P; ++e) {
         const uint32_t row = (p1[0][e] < N ? p1[0][e] : N - 1) / S.r;  // < m
 #pragma unroll
-        for (uint32_t b = 0; b < kDotMaxB; ++b) yv[e][b] = b < B ? Yhat[(size_t)b * m + row] : 0u;
+        for (uint32_t b = 0; b < MB; ++b) yv[e][b] = b < B ? Yhat[(size_t)b * m + row] : 0u;
     }
     synseg::seg_second_scan<1>(S, q, sg, lds, x);
     const uint32_t j0 = sg * synseg::kSegLen + threadIdx.x * P;
-    uint64_t t[kDotMaxB] = {};
+    uint64_t t[MB] = {};
 #pragma unroll
     for (int e = 0; e < P; ++e) {
         const uint32_t c = j0 + e < N ? fmul(w1[0][e], x[0][e]) : 0u;
 #pragma unroll
-        for (uint32_t b = 0; b < kDotMaxB; ++b) t[b] += ffold((uint64_t)c * yv[e][b]);
+        for (uint32_t b = 0; b < MB; ++b) t[b] += ffold((uint64_t)c * yv[e][b]);
     }
-    dot_add<synseg::kSegThreads / 64>(t, B, q, sg % nsub, accR, nsub, red);
+    dot_add<synseg::kSegThreads / 64, MB>(t, B, q, sg % nsub, accR, nsub, red);
     finish(B, S.count, nsub, accL, accR, ctrl, slots, nullptr, nullptr, vL, vR, accept, &last);
 }
 
@@ -1338,8 +1345,12 @@ hipError_t launch_decode_verify_syn(const uint32_t* PT, const uint32_t* Q, uint3
 
 bool dv_dot_fits(const mvk_key& key, uint32_t B, uint32_t ell, uint32_t ty, const uint32_t* Yhat, const uint32_t* Y) {
     const uint64_t Ny = (uint64_t)key.cy.r * key.m;
-    if (B == 0 || B > kDotMaxB || ell == 0 || ell > 4) return false;
-    if (Ny <= kSynScratchAbove && ty > kSortMax) return false;
+    if (B == 0 || ell == 0 || ell > 4) return false;
+    if (Ny > kSynScratchAbove) {
+        if (B > kDotMaxBLong || B * ell > kDotMaxSumsLong) return false;
+    } else if (ty > kSortMax || B > (Ny <= kDotSmall ? kDotMaxBSmall : kDotMaxB)) {
+        return false;
+    }
     const uintptr_t y = (uintptr_t)Y, h = (uintptr_t)Yhat, bytes = (uintptr_t)B * key.m * 4;
     if (Y && y < h + bytes && h < y + bytes) return false;  // Y over Yhat: the columns must be read before
     const uint64_t grid = ell * ((Ny + kFusedThreads - 1) / kFusedThreads) + ceil_div(key.n, kCols) +
@@ -1364,15 +1375,18 @@ hipError_t launch_decode_verify_dot(const mvk_key& key, const uint32_t* Xhat, co
         uint32_t slots = count_slots(counted);
         if (slots > l.slots) slots = l.slots;  // the layout holds this many counters
         const dim3 grid(counted + (Y ? B * nblkR : 0u));
-#define MVK_DOT(UU)                                                                                              \
-    hipLaunchKernelGGL((decode_verify_dot<UU>), grid, dim3(kFusedThreads), 0, s, key.PT, key.Q, m, n, Nx, Ny,     \
+#define MVK_DOT_B(UU, MB)                                                                                        \
+    hipLaunchKernelGGL((decode_verify_dot<UU, MB>), grid, dim3(kFusedThreads), 0, s, key.PT, key.Q, m, n, Nx, Ny,     \
                        Xhat, Yhat, B, ex.idx, ex.val, ex.t, ey.idx, ey.val, ey.t, ell, c.r, c.pi1, c.pi2, c.v1,   \
                        c.v2, Y, accL, accR, l.nsub, nblkR, nblkL, nseg, ctrl, slots, vL, vR, accept)
-        if (U == 8) MVK_DOT(8);
-        else if (U == 16) MVK_DOT(16);
-        else if (U == 24) MVK_DOT(24);
-        else MVK_DOT(32);
+#define MVK_DOT(UU) \
+    if (B <= 4) MVK_DOT_B(UU, 4); else MVK_DOT_B(UU, kDotMaxB)
+        if (U == 8) { MVK_DOT(8); }
+        else if (U == 16) { MVK_DOT(16); }
+        else if (U == 24) { MVK_DOT(24); }
+        else { MVK_DOT(32); }
 #undef MVK_DOT
+#undef MVK_DOT_B
         return hipGetLastError();
     }
     const uint32_t nseg = ceil_div(Ny, synseg::kSegLen);

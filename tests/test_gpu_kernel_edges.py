@@ -90,17 +90,19 @@ def test_prepare_split(m, n, rx, ry, B, tx, p):
     assert np.array_equal(host(prep.U), oracle.server_eval(np.ascontiguousarray(t.W.T), R, p=p))
 
 
-# Decode/verify without r_q (up to 8 columns, 4 repetitions and, in short blocks,
-# 64 terms): no noise, the most terms and one more; N around one segment
-# of 512 and of 1024 positions, 16384 (the last block of one workgroup) and one
-# more, long blocks with four columns per lane; the next column and repetition;
-# Y over Yhat.
+# Decode/verify without r_q (up to 4 repetitions; blocks up to 16384 positions: 64
+# terms and 16 columns, 8 up to 4096 positions; long ones: 4 columns and 8 sums):
+# no noise, the most terms, columns and repetitions and one more of each; N around
+# one segment of 512 and of 1024 positions, 16384 (the last block of one
+# workgroup) and one more; Y over Yhat.
 @pytest.mark.parametrize("m,n,rx,ry,B,tx,ty,ell,inplace", [
     (1, 1, 1, 1, 1, 0, 1, 1, False), (5, 3, 2, 3, 3, 6, 15, 4, False), (256, 256, 2, 2, 1, 8, 31, 2, False),
-    (257, 300, 2, 2, 8, 64, 64, 2, False), (171, 100, 3, 3, 2, 65, 65, 3, False), (1000, 700, 3, 4, 4, 128, 129, 2, False),
-    (500, 500, 3, 1, 1, 192, 192, 1, False), (600, 400, 3, 3, 1, 193, 193, 1, False), (300, 500, 2, 3, 9, 20, 31, 2, False),
-    (300, 500, 2, 3, 2, 20, 31, 5, False), (300, 500, 2, 3, 2, 20, 31, 2, True), (4096, 200, 3, 4, 1, 63, 63, 2, False),
-    (4097, 200, 3, 4, 1, 63, 63, 2, False), (5462, 4097, 4, 3, 3, 40, 31, 2, False), (8192, 5000, 4, 8, 8, 154, 200, 4, False),
+    (257, 300, 2, 2, 8, 64, 64, 2, False), (171, 100, 3, 3, 2, 65, 65, 3, False), (1000, 700, 3, 4, 4, 128, 64, 2, False),
+    (500, 500, 3, 1, 1, 192, 64, 1, False), (300, 500, 2, 3, 5, 20, 31, 4, False), (300, 500, 2, 3, 9, 20, 31, 2, False),
+    (300, 500, 2, 3, 2, 20, 31, 5, False), (300, 500, 2, 3, 2, 20, 31, 2, True), (4097, 200, 3, 1, 16, 9, 31, 4, False),
+    (4097, 200, 3, 1, 17, 9, 31, 2, False), (4096, 200, 3, 4, 9, 63, 63, 2, False), (4096, 200, 3, 1, 8, 63, 63, 2, False),
+    (4097, 200, 3, 4, 1, 63, 63, 2, False), (5462, 4097, 4, 3, 4, 40, 31, 2, False), (5462, 500, 4, 4, 3, 40, 31, 3, False),
+    (8192, 5000, 4, 8, 2, 154, 200, 4, False), (8192, 5000, 4, 8, 8, 154, 200, 4, False), (5000, 300, 2, 4, 5, 9, 31, 1, False),
     (9001, 300, 2, 2, 2, 30, 31, 2, True), (16384, 1000, 3, 8, 4, 8, 31, 2, False),
 ])
 @pytest.mark.parametrize("p", [synth.P, synth.P_BABYBEAR])
