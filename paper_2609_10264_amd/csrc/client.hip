@@ -564,7 +564,8 @@ struct TermSums {
 // (from the sorted terms, ty <= kSortMax) and its products with V2 at all N
 // positions: those that Pi2 sends into the segment go to LDS, those that it
 // sends behind it are added up to the segment's carry.  That repeats N
-// products per workgroup (1.2 us of one CU at N = 12288) and takes the place
+// products per workgroup (by instruction count about
+// 1 us of one CU at N = 12288) and takes the place
 // of a scan and two scatters of the whole block by one CU (about 10 us).
 constexpr uint32_t kSortMax = 64;
 template <int MB>
