@@ -512,7 +512,7 @@ PrepPlan plan_with_cols(PrepPlan pl, const PrepInputDesc* ins, uint32_t NI, cons
                         uint32_t cols) {
     PrepArgs& a = pl.a;
     uint64_t sx = 0, sy = 0, items = 0;
-    bool any_long = false;
+    uint64_t n_long = 0;  // vectors that run by segments anyway
     for (uint32_t j = 0; j < NI; ++j) {
         const PrepInputDesc& d = ins[j];
         PrepIn& in = a.in[j];
@@ -521,7 +521,7 @@ PrepPlan plan_with_cols(PrepPlan pl, const PrepInputDesc* ins, uint32_t NI, cons
         in.idx = d.idx, in.val = d.val, in.Mx = d.Mx;
         in.n = c->k, in.r = c->r, in.t = d.t, in.count = d.count;
         const uint64_t N = (uint64_t)c->k * c->r;
-        any_long = any_long || (d.count && !prep_short(N));
+        if (!prep_short(N)) n_long += d.count;
         if (d.count && prep_short(N)) {
             sx += d.count;
             pl.U = prep_u(N) > pl.U ? prep_u(N) : pl.U;
@@ -543,7 +543,7 @@ PrepPlan plan_with_cols(PrepPlan pl, const PrepInputDesc* ins, uint32_t NI, cons
         const uint64_t ix = (uint64_t)nx * pr.nbm, iy = (uint64_t)d.count * pr.nbn;
         pr.items_x = (uint32_t)(ix < 0xffffffffu ? ix : 0xffffffffu);
         const uint64_t N = (uint64_t)key.m * key.cy.r;
-        any_long = any_long || (d.count && !prep_short(N));
+        if (!prep_short(N)) n_long += d.count;
         if (d.count && prep_short(N)) {
             sy += d.count;
             pl.U = prep_u(N) > pl.U ? prep_u(N) : pl.U;
@@ -559,8 +559,9 @@ PrepPlan plan_with_cols(PrepPlan pl, const PrepInputDesc* ins, uint32_t NI, cons
     // In a split plan the short syndromes are a launch of their own, about 10 us
     // of a few compute units each.  Where long ones run by segments anyway the
     // short ones join them, up to as many as there are compute units (above,
-    // they fill the chip by themselves and their work arrays would grow large).
-    pl.join = pl.split && any_long && sy <= 256;
+    // they fill the chip by themselves and their work arrays would grow large)
+    // and as one sequence of launches takes them all.
+    pl.join = pl.split && n_long && sy <= 256 && n_long + sy <= synseg::kMaxVectors;
     pl.grid = pl.split ? items : sy + (items + kQuarters - 1) / kQuarters;
     pl.wide = cols == kWideCols;
     if (pl.split && pl.vec && !pl.wide) {
@@ -619,7 +620,7 @@ hipError_t launch_client_prepare_multi(const PrepInputDesc* ins, uint32_t NI, co
         if (!synseg::seg_args(sets, S, scratch, scratch_bytes, &sa)) return hipErrorInvalidValue;
         sh = synseg::seg_shape(sa);
         const uint64_t all = (uint64_t)sh.gx * sh.rows + pl.grid;
-        beside = pl.split && !(done && ndone) && sh.stripes == 1 && sh.rows && sh.rows <= 65535u && pl.grid &&
+        beside = pl.split && !(done && ndone) && sh.stripes == 1 && sh.rows && sh.rows <= synseg::kMaxVectors && pl.grid &&
                  all < 0x7fffff00u;
         const hipError_t e = beside ? synseg::launch_seg_first(sa, sh, s)
                                     : launch_syn_sets(sets, S, scratch, scratch_bytes, s);

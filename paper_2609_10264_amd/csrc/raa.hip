@@ -496,7 +496,7 @@ template <bool SPARSE>
 hipError_t launch_seg_sets(SegArgs a, hipStream_t s) {
     const SegShape h = seg_shape(a);
     if (h.rows == 0) return hipSuccess;
-    if (h.rows > 65535u) return hipErrorInvalidValue;
+    if (h.rows > kMaxVectors) return hipErrorInvalidValue;
     hipError_t e = launch_p1<SPARSE>(a, h, s);
     if (e != hipSuccess) return e;
     const dim3 grid(h.gx, h.rows);
@@ -715,7 +715,7 @@ SegShape seg_shape(SegArgs& a) {
     // placed by XCD: whole eights, and a rest of six or more (its empty places
     // return at once; fewer vectors would leave XCDs idle)
     a.by_xcd = (nv + 2) / kXcds * kXcds;
-    if (a.by_xcd > 65535u) a.by_xcd = nv / kXcds * kXcds;
+    if (a.by_xcd > kMaxVectors) a.by_xcd = nv / kXcds * kXcds;
     h.rows = nv > a.by_xcd ? nv : a.by_xcd;
     // four stripes per workgroup where one each would be more workgroups than
     // the chip holds at once (eight per compute unit)
@@ -752,7 +752,7 @@ bool synseg::seg_args(const SynSet* sets, uint32_t S, uint32_t* scratch, size_t 
         w += (syn_seg_bytes(d.count, N) + 255) & ~(size_t)255;
     }
     *out = a;
-    return nv <= 65535u;
+    return nv <= kMaxVectors;
 }
 
 hipError_t launch_syn_sets(const SynSet* sets, uint32_t S, uint32_t* scratch, size_t scratch_bytes, hipStream_t s) {

@@ -90,6 +90,8 @@ __device__ __forceinline__ void seg_suffix_scan(uint32_t (&x)[NS][kSegPer], uint
     }
 }
 
+// Vectors of one sequence of launches (grid.y).
+constexpr uint32_t kMaxVectors = 65535u;
 // A set of `count` vectors over one code, with its work region.
 struct SegSet {
     const uint32_t *pi1, *pi2, *v1, *v2;

@@ -1,0 +1,85 @@
+"""The library's host side without a GPU: which kernels a call launches with
+which grids, what scratch it asks for, and what it does when the runtime refuses
+something.  Each check runs in a child process whose HIP runtime is the recorder
+of tests/hip_record/ (nothing is computed; device pointers are never read)."""
+import json
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+REC = os.path.join(HERE, "hip_record")
+
+PRELUDE = """
+import ctypes, importlib.util, json, sys
+rec = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+rec.rec_name.restype = ctypes.c_char_p
+rec.rec_malloc_limit.argtypes = [ctypes.c_uint64]
+spec = importlib.util.spec_from_file_location("mvk_lib", sys.argv[2])
+L = importlib.util.module_from_spec(spec)
+spec.loader.exec_module(L)
+lib = L.load(int(sys.argv[3]))
+assert any(sys.argv[1] in l for l in open("/proc/self/maps"))
+next_ptr = [1 << 40]
+def ptr():  # an aligned device address that nothing reads
+    next_ptr[0] += 1 << 36
+    return next_ptr[0]
+def code(k, r): return L.MvkCode(k, r, ptr(), ptr(), ptr(), ptr())
+def key(m, n, rx, ry): return L.MvkKey(m, n, code(n, rx), code(m, ry), ptr(), ptr())
+def sparse(count, t): return L.MvkSparse(ptr(), ptr(), t, count)
+def launches():
+    out = []
+    for i in range(rec.rec_count()):
+        g = (ctypes.c_uint32 * 3)()
+        rec.rec_grid(i, g)
+        out.append([rec.rec_name(i).decode().replace("void ", "").replace("mvk::(anonymous namespace)::", "").split("(")[0],
+                    g[0], g[1]])
+    return out
+ref = ctypes.byref
+result = {}
+"""
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    cxx = shutil.which("g++")
+    if not cxx:
+        pytest.skip("g++ not found")
+    d = tmp_path_factory.mktemp("hip_record")
+    so = str(d / "libamdhip64.so.7")
+    r = subprocess.run([cxx, "-O1", "-std=c++17", "-shared", "-fPIC", "-Wl,-soname,libamdhip64.so.7",
+                        f"-Wl,--version-script={REC}/hip_record.map", "-o", so, f"{REC}/hip_record.cpp"],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    lib = os.path.join(ROOT, "paper_2609_10264_amd", "_lib.py")
+
+    def run(body, p=2**31 - 1):
+        if not os.path.exists(os.path.join(ROOT, "paper_2609_10264_amd", "libmvk.so")):
+            pytest.skip("libmvk.so not built")
+        r = subprocess.run([sys.executable, "-c", PRELUDE + body + "\nprint(json.dumps(result))\n", so, lib, str(p)],
+                           capture_output=True, text=True, timeout=60)
+        assert r.returncode == 0, r.stderr[-2000:]
+        return json.loads(r.stdout.splitlines()[-1])
+
+    return run
+
+
+# Short syndromes join the long ones only while all of them fit one sequence of
+# launches (65535 vectors): 65533 long noise vectors and two short challenges do,
+# 65534 and 65535 do not, and the call must go on as two launches.
+@pytest.mark.parametrize("B", [65533, 65534, 65535])
+def test_prepare_most_columns(host, B):
+    out = host(f"""
+k = key(16, 16400, 2, 2)
+ex, ey = sparse({B}, 8), sparse(2, 8)
+result["st"] = lib.mvk_client_prepare(ref(k), ref(ex), ref(ey), ptr(), ptr(), ptr(), ptr(), None, 0, None)
+result["launches"] = launches()
+""")
+    assert out["st"] == 0
+    names = [l[0] for l in out["launches"]]
+    assert any(n.startswith("client_prepare_kernel") for n in names) == (B > 65533), names
+    assert sum(n.startswith("syn_p1") for n in names) == 1 and sum("syn_p3" in n for n in names) == 1
