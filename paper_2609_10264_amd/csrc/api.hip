@@ -397,23 +397,29 @@ mvk_status mvk_keygen(const mvk_key* key, const int8_t* W, void* stream) {
         bool seg;
         size_t bytes, ctrl_words, t3_bytes;
     } f[2];
-    for (int i = 0; i < 2; ++i) {
-        const mvk_code& c = i ? key->cy : key->cx;
-        const uint32_t nvec = i ? n : m;
-        const bool aligned = c.k % 16 == 0 && (i || (uintptr_t)W % 16 == 0);  // (W^T starts aligned)
-        const size_t N = (size_t)c.k * c.r;
-        f[i].ctrl_words = 0;
-        f[i].t3_bytes = 0;
-        f[i].seg = enc_i8_scratch(c.k, c.r, nvec, aligned, &f[i].bytes, &f[i].ctrl_words);
-        if (!f[i].seg) {
-            f[i].t3_bytes = align_up(N * nvec * sizeof(uint32_t));
-            f[i].bytes = f[i].t3_bytes + encT_seg_words(N, nvec) * sizeof(uint32_t);
-        }
-    }
-    const size_t sc_bytes = std::max(f[0].bytes, f[1].bytes);
     void* ws = nullptr;
     uint32_t* ctrl = nullptr;
-    st = workspace(s, wt_bytes + sc_bytes, &ws, &ctrl, kCtrlBase + 4 * std::max(f[0].ctrl_words, f[1].ctrl_words));
+    // The segmented form needs more of the workspace (t3 in whole tiles, the
+    // offsets): where that cannot be had, on a nearly full card or because the
+    // stream is capturing, the other one does.
+    for (bool seg : {true, false}) {
+        for (int i = 0; i < 2; ++i) {
+            const mvk_code& c = i ? key->cy : key->cx;
+            const uint32_t nvec = i ? n : m;
+            const bool aligned = c.k % 16 == 0 && (i || (uintptr_t)W % 16 == 0);  // (W^T starts aligned)
+            const size_t N = (size_t)c.k * c.r;
+            f[i].ctrl_words = 0;
+            f[i].t3_bytes = 0;
+            f[i].seg = seg && enc_i8_scratch(c.k, c.r, nvec, aligned, &f[i].bytes, &f[i].ctrl_words);
+            if (!f[i].seg) {
+                f[i].t3_bytes = align_up(N * nvec * sizeof(uint32_t));
+                f[i].bytes = f[i].t3_bytes + encT_seg_words(N, nvec) * sizeof(uint32_t);
+            }
+        }
+        st = workspace(s, wt_bytes + std::max(f[0].bytes, f[1].bytes), &ws, &ctrl,
+                       kCtrlBase + 4 * std::max(f[0].ctrl_words, f[1].ctrl_words));
+        if ((st != MVK_ENOMEM && st != MVK_ECAPTURE) || !(f[0].seg || f[1].seg)) break;
+    }
     if (st) return st;
     uint32_t* counters = (uint32_t*)((char*)ctrl + kCtrlBase);
     int8_t* WT = (int8_t*)ws;

@@ -83,3 +83,31 @@ result["launches"] = launches()
     names = [l[0] for l in out["launches"]]
     assert any(n.startswith("client_prepare_kernel") for n in names) == (B > 65533), names
     assert sum(n.startswith("syn_p1") for n in names) == 1 and sum("syn_p3" in n for n in names) == 1
+
+
+# keygen where the workspace cannot hold the segmented encoding (a nearly full
+# card; a stream that captures and has had a smaller workspace): the form that
+# needs m*n + max(Nx*m, Ny*n)*4 bytes and 1/32 (the segment sums) takes its place.
+@pytest.mark.parametrize("how", ["full", "capture"])
+def test_keygen_scratch(host, how):
+    out = host(f"""
+m, n, r = 2049, 8192, 3
+k = key(m, n, r, r)
+need = int((m * n + 4 * r * m * n) * 1.034)
+if {how!r} == "full":
+    rec.rec_malloc_limit(need)
+else:
+    # 2N + (segments + 1) * 2 words of workspace per vector: 2 vectors of N = need / 16
+    N = need // 16
+    assert lib.mvk_raa_syndrome(ref(code(N, 1)), ptr(), 2, ptr(), None) == 0
+    rec.rec_reset()
+    rec.rec_capture(1)
+result["st"] = lib.mvk_keygen(ref(k), ptr(), None)
+result["launches"] = launches()
+rec.rec_reset()
+result["free"] = lib.mvk_keygen(ref(k), ptr(), None)
+result["then"] = launches()
+""")
+    assert out["st"] == 0 and out["free"] == 0
+    assert [l[0] for l in out["launches"] if "fill" not in l[0]][1].startswith("enc_pass1")
+    assert any(l[0].startswith("enc_seg") for l in out["then"])
