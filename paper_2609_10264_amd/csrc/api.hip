@@ -92,6 +92,16 @@ mvk_status workspace(hipStream_t s, size_t bytes, void** out, uint32_t** ctrl = 
     return MVK_OK;
 }
 
+// workspace() for a call that can do with less: *bytes of it, or, where they cannot
+// be had (a nearly full card, a stream that is capturing), `least` bytes, set in
+// *bytes.
+mvk_status workspace_or(hipStream_t s, size_t* bytes, size_t least, void** out, uint32_t** ctrl, size_t ctrl_bytes) {
+    const mvk_status st = workspace(s, *bytes, out, ctrl, ctrl_bytes);
+    if ((st != MVK_ENOMEM && st != MVK_ECAPTURE) || least >= *bytes) return st;
+    *bytes = least;
+    return workspace(s, least, out, ctrl, ctrl_bytes);
+}
+
 inline mvk_status hip_status(hipError_t e) { return e == hipSuccess ? MVK_OK : MVK_EHIP; }
 
 // MVK_VALIDATE=1 in the environment: the pvMVMD calls check that their field
@@ -595,10 +605,11 @@ mvk_status mvk_client_prepare(const mvk_key* key, const mvk_sparse* ex, const mv
     }
     hipStream_t s = (hipStream_t)stream;
     if (nx == 0 && ny == 0) return done_flag ? hip_status(launch_flag_signal(done_flag, done_value, s)) : MVK_OK;
-    const size_t scratch = prep_scratch_bytes(&key, 1, nx, ny);
+    size_t scratch = prep_scratch_bytes(&key, 1, nx, ny, false);
     void* ws = nullptr;
     uint32_t* ctrl = nullptr;
-    st = workspace(s, scratch, &ws, &ctrl, 4 * (kPrepCounterWord + prep_ctrl_words(*key, nx, ny)));
+    st = workspace_or(s, &scratch, prep_scratch_bytes(&key, 1, nx, ny, true), &ws, &ctrl,
+                      4 * (kPrepCounterWord + prep_ctrl_words(*key, nx, ny)));
     if (st) return st;
     return hip_status(launch_client_prepare(*key, nx ? ex->idx : nullptr, nx ? ex->val : nullptr, nx ? ex->t : 0u,
                                             nx, ny ? ey->idx : nullptr, ny ? ey->val : nullptr, ny ? ey->t : 0u, ny,
@@ -653,10 +664,11 @@ mvk_status mvk_client_prepare_group(uint32_t G, const mvk_key* const* keys, cons
     }
     hipStream_t s = (hipStream_t)stream;
     if (nx == 0 && ny == 0) return done_flag ? hip_status(launch_flag_signal(done_flag, done_value, s)) : MVK_OK;
-    const size_t scratch = prep_scratch_bytes(keys, G, nx, ny);
+    size_t scratch = prep_scratch_bytes(keys, G, nx, ny, false);
     void* ws = nullptr;
     uint32_t* ctrl = nullptr;
-    mvk_status st = workspace(s, scratch, &ws, &ctrl, 4 * (kPrepCounterWord + prep_ctrl_words(keys, G, nx, ny)));
+    mvk_status st = workspace_or(s, &scratch, prep_scratch_bytes(keys, G, nx, ny, true), &ws, &ctrl,
+                                 4 * (kPrepCounterWord + prep_ctrl_words(keys, G, nx, ny)));
     if (st) return st;
     return hip_status(launch_client_prepare_group(G, keys, nx ? ex->idx : nullptr, nx ? ex->val : nullptr,
                                                   nx ? ex->t : 0u, nx, eyi, eyv, ty, ny, Mx, My, R, U,
@@ -725,8 +737,9 @@ mvk_status mvk_client_prepare_multi(uint32_t G, const mvk_key* const* keys, cons
     }
     void* ws = nullptr;
     uint32_t* ctrl = nullptr;
-    const size_t scratch = prep_scratch_bytes(ins, NI, probs, G);
-    const mvk_status st = workspace(s, scratch, &ws, &ctrl, 4 * (kPrepCounterWord + prep_ctrl_words(ins, NI, probs, G)));
+    size_t scratch = prep_scratch_bytes(ins, NI, probs, G, false);
+    const mvk_status st = workspace_or(s, &scratch, prep_scratch_bytes(ins, NI, probs, G, true), &ws, &ctrl,
+                                       4 * (kPrepCounterWord + prep_ctrl_words(ins, NI, probs, G)));
     if (st) return st;
     return hip_status(launch_client_prepare_multi(ins, NI, probs, G, (uint32_t*)ws, scratch, &ctrl[kPrepCounterWord],
                                                   nflags ? flags : nullptr, nflags, done_value, s));

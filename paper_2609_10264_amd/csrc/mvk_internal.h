@@ -168,8 +168,8 @@ hipError_t launch_decode_verify_masked_group(uint32_t G, uint32_t m, uint32_t n,
 
 // prepare.hip ---------------------------------------------------------------
 // Mx, My for nx noise vectors and R, U for ny challenges (either count may
-// be 0).  scratch: scratch_bytes of at least prep_scratch_bytes (the work
-// regions of the syndromes longer than kSynScratchAbove, one after another).  done (may be null): set to
+// be 0).  scratch: prep_scratch_bytes (the work regions of the syndromes that
+// run by segments, one after another).  done (may be null): set to
 // done_value once every output is stored and visible device-wide; counter:
 // prep_ctrl_words(key, nx, ny) words of completion counters (count.h), zero
 // before the launch (left zero).
@@ -178,8 +178,10 @@ size_t prep_ctrl_words(const mvk_key& key, uint32_t nx, uint32_t ny);
 // each): input j holds `count` noise vectors of `t` terms over the privacy
 // code cx (Mx: count x cx->k); key g the output masks My of the noise of input
 // `in` (kPrepNoInput: none) and `count` challenges with R, U.  Syndromes
-// longer than kSynScratchAbove run first in their own launches (scratch of
-// prep_scratch_bytes); done: ndone device words, each set to done_value once
+// longer than kSynScratchAbove run by segments (syn_seg.h), before the gathers
+// or in part beside them; shorter ones join them where the plan says so and
+// scratch_bytes allows it.  prep_scratch_bytes: for every syndrome that would
+// run by segments, or (least) for the long ones alone; done: ndone device words, each set to done_value once
 // every output is stored and visible device-wide; counter: prep_ctrl_words
 // words, zero before the launch (left zero).
 constexpr uint32_t kMaxPrep = MVK_MAX_PREP;
@@ -198,9 +200,9 @@ struct PrepProbDesc {
     uint32_t *My, *R, *U;
 };
 size_t prep_ctrl_words(const PrepInputDesc* ins, uint32_t NI, const PrepProbDesc* probs, uint32_t G);
-size_t prep_scratch_bytes(const PrepInputDesc* ins, uint32_t NI, const PrepProbDesc* probs, uint32_t G);
+size_t prep_scratch_bytes(const PrepInputDesc* ins, uint32_t NI, const PrepProbDesc* probs, uint32_t G, bool least);
 // the same for G keys sharing one input of nx noise vectors, ny challenges each
-size_t prep_scratch_bytes(const mvk_key* const* keys, uint32_t G, uint32_t nx, uint32_t ny);
+size_t prep_scratch_bytes(const mvk_key* const* keys, uint32_t G, uint32_t nx, uint32_t ny, bool least);
 hipError_t launch_client_prepare_multi(const PrepInputDesc* ins, uint32_t NI, const PrepProbDesc* probs, uint32_t G,
                                        uint32_t* scratch, size_t scratch_bytes, uint32_t* counter,
                                        uint32_t* const* done, uint32_t ndone, uint32_t done_value, hipStream_t s);

@@ -597,9 +597,10 @@ uint32_t seg_sets(const PrepInputDesc* ins, uint32_t NI, const PrepProbDesc* pro
 }
 }  // namespace
 
-size_t prep_scratch_bytes(const PrepInputDesc* ins, uint32_t NI, const PrepProbDesc* probs, uint32_t G) {
+size_t prep_scratch_bytes(const PrepInputDesc* ins, uint32_t NI, const PrepProbDesc* probs, uint32_t G, bool least) {
     SynSet sets[2 * kMaxPrep];
-    return syn_sets_scratch_bytes(sets, seg_sets(ins, NI, probs, G, prep_plan(ins, NI, probs, G).join, sets));
+    const bool join = !least && prep_plan(ins, NI, probs, G).join;
+    return syn_sets_scratch_bytes(sets, seg_sets(ins, NI, probs, G, join, sets));
 }
 
 hipError_t launch_client_prepare_multi(const PrepInputDesc* ins, uint32_t NI, const PrepProbDesc* probs, uint32_t G,
@@ -609,7 +610,11 @@ hipError_t launch_client_prepare_multi(const PrepInputDesc* ins, uint32_t NI, co
     PrepPlan pl = prep_plan(ins, NI, probs, G);
     // syndromes by segments run first, all of them in one sequence of launches
     SynSet sets[2 * kMaxPrep];
-    const uint32_t S = seg_sets(ins, NI, probs, G, pl.join, sets);
+    uint32_t S = seg_sets(ins, NI, probs, G, pl.join, sets);
+    if (pl.join && syn_sets_scratch_bytes(sets, S) > scratch_bytes) {  // the caller had the least of it
+        pl.join = false;
+        S = seg_sets(ins, NI, probs, G, false, sets);
+    }
     // the second pass goes with the gathers (client_gather_pass_kernel) where
     // these have their own launch and nobody waits for a flag, which the last
     // gather would set
@@ -722,13 +727,13 @@ size_t prep_ctrl_words(const mvk_key* const* keys, uint32_t G, uint32_t nx, uint
     return prep_ctrl_words(&in, 1, probs, G);
 }
 
-size_t prep_scratch_bytes(const mvk_key* const* keys, uint32_t G, uint32_t nx, uint32_t ny) {
+size_t prep_scratch_bytes(const mvk_key* const* keys, uint32_t G, uint32_t nx, uint32_t ny, bool least) {
     if (G == 0 || G > kMaxPrep) return 0;
     PrepInputDesc in;
     PrepProbDesc probs[kMaxPrep];
     group_descs(G, keys, nullptr, nullptr, 0u, nx, nullptr, nullptr, 0u, ny, nullptr, nullptr, nullptr, nullptr, &in,
                 probs);
-    return prep_scratch_bytes(&in, 1, probs, G);
+    return prep_scratch_bytes(&in, 1, probs, G, least);
 }
 
 size_t prep_ctrl_words(const mvk_key& key, uint32_t nx, uint32_t ny) {

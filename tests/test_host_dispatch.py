@@ -111,3 +111,39 @@ result["then"] = launches()
     assert out["st"] == 0 and out["free"] == 0
     assert [l[0] for l in out["launches"] if "fill" not in l[0]][1].startswith("enc_pass1")
     assert any(l[0].startswith("enc_seg") for l in out["then"])
+
+
+# client_prepare where the workspace cannot hold the short syndromes beside the
+# long ones: they keep their own launch, which needs none.
+@pytest.mark.parametrize("call", ["one", "group", "multi"])
+@pytest.mark.parametrize("how", ["full", "capture"])
+def test_prepare_scratch(host, call, how):
+    out = host(f"""
+m, n, B, call = 8190, 9000, 64, {call!r}  # N = 16380 (short), 18000 (long)
+k = key(m, n, 2, 2)
+ex, ey = sparse(B, 8), sparse(16, 8)
+def run():
+    mx, my, r, u = ptr(), ptr(), ptr(), ptr()
+    if call == "one":
+        return lib.mvk_client_prepare(ref(k), ref(ex), ref(ey), mx, my, r, u, None, 0, None)
+    P1 = lambda a: (ctypes.c_void_p * 1)(a)
+    S1 = lambda a: (ctypes.POINTER(type(a)) * 1)(ctypes.pointer(a))
+    keys, eys = S1(k), S1(ey)
+    if call == "group":
+        return lib.mvk_client_prepare_group(1, keys, ref(ex), eys, mx, P1(my), P1(r), P1(u), None, 0, None)
+    return lib.mvk_client_prepare_multi(1, keys, S1(ex), eys, P1(mx), P1(my), P1(r), P1(u), None, 0, None)
+# the long vectors' work arrays, and 1 MiB for everything else
+rec.rec_malloc_limit(B * (2 * 18000 * 4 + 152) + (1 << 20))
+if {how!r} == "capture":  # the call before sizes the workspace
+    assert run() == 0
+    rec.rec_reset()
+    rec.rec_capture(1)
+result["st"] = run()
+result["launches"] = launches()
+rec.rec_reset()
+result["free"] = run()
+result["then"] = launches()
+""")
+    assert out["st"] == 0 and out["free"] == 0, out
+    assert any(l[0].startswith("client_prepare_kernel") for l in out["launches"])
+    assert not any(l[0].startswith("client_prepare_kernel") for l in out["then"])
