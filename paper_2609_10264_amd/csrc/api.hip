@@ -925,13 +925,15 @@ mvk_status mvk_batch_verify(const mvk_code* cy, const mvk_code* c2, const uint32
     const size_t r_bytes = align_up((size_t)ell * m * 4), rs_bytes = align_up((size_t)ell2 * Bn * 4);
     // Primary syndromes R_q = G e_q and secondary syndromes r_j = G' e'_j: where
     // either is long, both by segments in one sequence of launches (four claims
-    // of 4096 x 4096: the short one took 10 us by itself), else one launch each.
+    // of 4096 x 4096: the short one took 10 us by itself), else, and where the
+    // workspace for both cannot be had, one after the other.
     SynSet sets[2] = {{cy, e->idx, e->val, e->t, ell, nullptr}, {c2, e2->idx, e2->val, e2->t, ell2, nullptr}};
-    const bool by_seg = N > kSynScratchAbove || N2 > kSynScratchAbove;
-    const size_t syn_bytes = by_seg ? syn_sets_scratch_bytes(sets, 2) : 0;
+    const size_t in_turn = r_bytes + rs_bytes + std::max(syn_scratch_bytes(ell, N), syn_scratch_bytes(ell2, N2));
+    const size_t both = r_bytes + rs_bytes + syn_sets_scratch_bytes(sets, 2);
+    size_t ws_bytes = N > kSynScratchAbove || N2 > kSynScratchAbove ? both : in_turn;
     void* ws = nullptr;
     uint32_t* ctrl = nullptr;
-    st = workspace(s, r_bytes + rs_bytes + syn_bytes, &ws, &ctrl, batch_ctrl_bytes(m, n, B, ell, ell2));
+    st = workspace_or(s, &ws_bytes, in_turn, &ws, &ctrl, batch_ctrl_bytes(m, n, B, ell, ell2));
     if (st) return st;
     uint32_t* R = (uint32_t*)ws;
     uint32_t* Rs = (uint32_t*)((char*)ws + r_bytes);
@@ -939,8 +941,8 @@ mvk_status mvk_batch_verify(const mvk_code* cy, const mvk_code* c2, const uint32
     sets[0].out = R;
     sets[1].out = Rs;
     hipError_t err;
-    if (by_seg) {
-        err = launch_syn_sets(sets, 2, scratch, syn_bytes, s);
+    if (ws_bytes == both) {
+        err = launch_syn_sets(sets, 2, scratch, both - r_bytes - rs_bytes, s);
     } else {
         err = launch_syn_sparse(*cy, e->idx, e->val, e->t, ell, nullptr, scratch, R, s);
         if (err == hipSuccess) err = launch_syn_sparse(*c2, e2->idx, e2->val, e2->t, ell2, nullptr, scratch, Rs, s);

@@ -147,3 +147,29 @@ result["then"] = launches()
     assert out["st"] == 0 and out["free"] == 0, out
     assert any(l[0].startswith("client_prepare_kernel") for l in out["launches"])
     assert not any(l[0].startswith("client_prepare_kernel") for l in out["then"])
+
+
+# batch_verify likewise: the short code's syndromes in their own launch.
+@pytest.mark.parametrize("how", ["full", "capture"])
+def test_batch_scratch(host, how):
+    out = host(f"""
+m, n, B, ell = 9000, 1000, 8, 16  # N = 18000 (long), 16000 (short)
+cy, c2 = code(m, 2), code(B * n, 2)
+e, e2 = sparse(ell, 8), sparse(ell, 8)
+run = lambda: lib.mvk_batch_verify(ref(cy), ref(c2), ptr(), m, n, B, ptr(), ptr(), ref(e), ptr(), ref(e2), None, None,
+                                   None, None, ptr(), None)
+need = ell * (2 * 18000 * 4 + 152) + 4 * ell * (m + B * n) + (1 << 20)
+rec.rec_malloc_limit(need)
+if {how!r} == "capture":  # the call before sizes the workspace
+    assert run() == 0
+    rec.rec_reset()
+    rec.rec_capture(1)
+result["st"] = run()
+result["launches"] = launches()
+rec.rec_reset()
+result["free"] = run()
+result["then"] = launches()
+""")
+    assert out["st"] == 0 and out["free"] == 0, out
+    assert any(l[0].startswith("syn_wg") for l in out["launches"])
+    assert not any(l[0].startswith("syn_wg") for l in out["then"])
