@@ -1406,7 +1406,10 @@ hipError_t launch_decode_verify_dot(const mvk_key& key, const uint32_t* Xhat, co
     if (slots > l.slots) slots = l.slots;
     hipLaunchKernelGGL(decode_verify_long2, dim3(ell * nseg), dim3(synseg::kSegThreads), 0, s, S, m, Yhat, B, accL,
                        accR, l.nsub, nseg, ctrl, slots, vL, vR, accept);
-    return hipGetLastError();
+    e = hipGetLastError();
+    // (refused: the sums that the first launch adds must not wait for the next call)
+    if (e != hipSuccess) (void)launch_fill_u32((uint32_t*)accL, (size_t)2 * ell * B * l.nsub, 0u, s);
+    return e;
 }
 
 hipError_t launch_decode_verify(const uint32_t* PT, const uint32_t* Q, uint32_t m, uint32_t n, uint32_t Nx,

@@ -173,3 +173,19 @@ result["then"] = launches()
     assert out["st"] == 0 and out["free"] == 0, out
     assert any(l[0].startswith("syn_wg") for l in out["launches"])
     assert not any(l[0].startswith("syn_wg") for l in out["then"])
+
+
+# decode/verify of a long block whose second launch is refused: the first has
+# added to accumulators that the second would have cleared, so they are cleared
+# before the call returns (else the next verification on the stream rejects).
+def test_refused_second_launch_leaves_no_sums(host):
+    out = host("""
+k = key(16400, 300, 2, 2)
+ex, ey = sparse(2, 8), sparse(2, 8)
+rec.rec_refuse_launch(2)  # after the fill of the new control region and the first launch
+result["st"] = lib.mvk_decode_verify(ref(k), ptr(), ptr(), 2, ref(ex), ref(ey), ptr(), None, None, ptr(), None)
+result["launches"] = launches()
+""")
+    assert out["st"] == -4
+    names = [l[0].split("<")[0] for l in out["launches"]]
+    assert names == ["fill_u32", "decode_verify_long1", "refused", "fill_u32"]
