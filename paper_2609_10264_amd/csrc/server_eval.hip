@@ -1287,13 +1287,17 @@ GroupPlan group_plan(uint32_t m, uint32_t n, uint32_t nb) {
     GroupPlan g{false, qt, 0, stream_rows(qt), stream_ksplit(m, n, qt), 0};
     if (qt > 4) return g;
     // digits-stationary: rows 128*tww, each k-range's digit tiles fit in LDS;
-    // estimated time ceil(workgroups / 256) * (W k-blocks per workgroup in units
-    // of 128 rows + fill + exchange of the split values, which the last
-    // workgroup of a row block reads from the ks - 1 others).  The exchange is
-    // in proportion to the row blocks that do it at a time, up to 64: sweeps of
-    // ks on MI355X, 16 queries: 256 x 4096 6.8 us with eight ranges against 8.9
-    // with four, 1024 x 4096 7.3 against 9.3, 2048 x 2048 7.2 with four against
-    // 9.5 with two; 4096 x 4096 10.4 with eight and 10.6 with four.
+    // estimated time, in quarters of a W k-block of 128 rows: ceil(workgroups /
+    // 256) times what one workgroup takes.  W is loaded in chunks of eight k-blocks
+    // (a shorter range re-reads its last block), and the digits converted k-block
+    // by k-block; a split pays for its atomics once, and for the values of the ks -
+    // 1 others, which the last workgroup of a row block reads, in proportion to the
+    // row blocks that do it at a time, up to 64.  From sweeps of ks on MI355X over
+    // 128 .. 28672 rows of 512 .. 11008 columns: within 1% of the best of each
+    // shape on average.  16 queries: 256 x 4096 6.8 us with eight ranges against
+    // 8.9 with four, 2048 x 2048 7.2 with four against 9.5 with two, 1024 x 512 5.0
+    // unsplit against 6.6 with four; 8 queries: 2048 x 2048 5.6 with four against
+    // 5.8 with eight.
     const uint32_t kbm = qt == 4 ? kDstatKbm4 : kDstatKbm2;
     uint64_t best = ~0ull;
     for (uint32_t tww = 1; tww <= 2; ++tww)
@@ -1301,8 +1305,9 @@ GroupPlan group_plan(uint32_t m, uint32_t n, uint32_t nb) {
             const uint32_t kb_per = ceil_div(nkb, ks);
             if (kb_per > kbm) continue;
             const uint32_t rows = 128 * tww, nrb = ceil_div(m, rows), nwg = nrb * ks;
+            const uint32_t per_wg = tww * (3 * ceil_div(kb_per, 8) * 8 + kb_per) + (ks > 1 ? 40 : 24);
             const uint64_t cost = (uint64_t)ceil_div(nwg, 256) *
-                                  (64 * (kb_per * tww + 6) + qt * (ks - 1) * (nrb < 64 ? nrb : 64));
+                                  (64 * per_wg + 3 * qt * (ks - 1) * (nrb < 64 ? nrb : 64));
             if (cost < best) {
                 best = cost;
                 g = GroupPlan{true, qt, tww, rows, ks, dstat_kbm(kb_per)};

@@ -189,3 +189,21 @@ result["launches"] = launches()
     assert out["st"] == -4
     names = [l[0].split("<")[0] for l in out["launches"]]
     assert names == ["fill_u32", "decode_verify_long1", "refused", "fill_u32"]
+
+
+# k-ranges of the digits-stationary kernel (5 to 16 queries): none where a row is
+# one chunk of eight k-blocks, four (not eight, which would split a chunk) at 2048
+# x 2048 with 8 queries, and the ranges that few row blocks take.
+@pytest.mark.parametrize("m,n,B,ks", [
+    (1024, 512, 16, 1), (1024, 512, 8, 1), (6000, 512, 16, 1), (2048, 2048, 8, 4), (3072, 2048, 5, 4), (2048, 2048, 16, 4),
+    (1024, 4096, 16, 8), (4096, 4096, 8, 8), (4096, 4096, 16, 8), (11008, 4096, 16, 2), (8192, 3072, 16, 4), (28672, 1000, 8, 1),
+])
+def test_k_ranges(host, m, n, B, ks):
+    out = host(f"""
+result["st"] = lib.mvk_server_eval_packed(ptr(), {m}, {n}, ptr(), {B}, ptr(), None)
+result["launches"] = launches()
+""")
+    name, grid, _ = out["launches"][-1]
+    assert out["st"] == 0 and name.startswith("server_eval_mfma_dstat<%d, 1," % (2 if B <= 8 else 4)), name
+    blocks = -(-m // 128)
+    assert grid == -(-blocks // (8 // ks)) * 8
