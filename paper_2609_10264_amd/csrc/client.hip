@@ -506,7 +506,8 @@ __global__ __launch_bounds__(kFusedThreads) void decode_verify_syn(
 //
 // Adds the sums over the workgroup of x[b] (b < MB; columns < B) to
 // accumulator (q, b, sub).  NW waves.
-constexpr uint32_t kDotMaxB = 16, kDotMaxBSmall = 8, kDotSmall = 4096, kDotMaxBLong = 4, kDotMaxSumsLong = 8;
+constexpr uint32_t kDotMaxB = 16, kDotMaxBSmall = 8, kDotSmall = 4096, kDotMaxBLong = 4, kDotMaxSumsLong = 8,
+                   kDotFewCols = 8192;
 template <int NW, int MB>
 __device__ __forceinline__ void dot_add(const uint64_t (&x)[MB], uint32_t B, uint32_t q, uint32_t sub,
                                         unsigned long long* accR, uint32_t nsub, uint64_t (*red)[MB]) {
@@ -1352,6 +1353,21 @@ bool dv_dot_fits(const mvk_key& key, uint32_t B, uint32_t ell, uint32_t ty, cons
     } else if (ty > kSortMax || B > (Ny <= kDotSmall ? kDotMaxBSmall : kDotMaxB)) {
         return false;
     }
+    // Where decode_verify_syn takes four columns a lane and all of it is resident, it
+    // does not grow with B, and 1.4 us with every repetition, the dot form 0.5 us
+    // with every column: up to 8192 positions it is the faster one from 13
+    // columns with one repetition and from 16 with two (4096 x 4096, r = 2, 16
+    // columns: 15.1 us against 16.5 with one, 15.8 against 16.5 with two, 18.6
+    // against 16.9 with four; 5000 x 3000, r = 1, 14 columns, one repetition: 14.1
+    // against 14.7).  Without Y the dot form has no decode role and is as fast or
+    // faster with r = 1 (5000 x 3000, 16 columns: 13.9 and 14.0 with one, 15.3
+    // against 14.6 with two), not with r = 2 (4096 x 4096: 13.4 against 15.4).
+    // With one column a lane the dot form keeps all of its range (one repetition
+    // and 16 columns are even: 14.1 and 13.1 us at 520 x 512, r = 8, 13.8 and 14.1
+    // at 1366 x 4096, r = 3, 15.7 and 16.2 at 1000 x 16000, r = 8).
+    if ((Y || key.cy.r > 1) && Ny <= kDotFewCols && B >= 10 + 3 * ell &&
+        dv_decode_cols(key.m, B, key.PT, Yhat, Y, key.PT) == 4 && dv_syn_fits(key.m, key.n, (uint32_t)Ny, B, ell, 4))
+        return false;
     const uintptr_t y = (uintptr_t)Y, h = (uintptr_t)Yhat, bytes = (uintptr_t)B * key.m * 4;
     if (Y && y < h + bytes && h < y + bytes) return false;  // Y over Yhat: the columns must be read before
     const uint64_t grid = ell * ((Ny + kFusedThreads - 1) / kFusedThreads) + ceil_div(key.n, kCols) +

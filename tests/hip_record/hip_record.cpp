@@ -26,7 +26,7 @@ std::vector<std::pair<Dim3, Dim3>> configs;
 std::vector<size_t> config_shm;
 long refuse_at = -1;       // index of the launch to refuse
 uint64_t malloc_limit = ~0ull, malloc_next = 1ull << 44;
-int capture = 0;
+int capture = 0, occupancy = 1;
 constexpr int kErrorMemory = 2, kErrorLaunch = 719;
 }  // namespace
 
@@ -35,6 +35,7 @@ void rec_reset() { launches.clear(); refuse_at = -1; malloc_limit = ~0ull; captu
 void rec_refuse_launch(long i) { refuse_at = i; }
 void rec_malloc_limit(uint64_t b) { malloc_limit = b; }
 void rec_capture(int on) { capture = on; }
+void rec_occupancy(int blocks) { occupancy = blocks; }
 long rec_count() { return (long)launches.size(); }
 const char* rec_name(long i) { return launches[i].name.c_str(); }
 void rec_grid(long i, uint32_t* g) { g[0] = launches[i].grid.x, g[1] = launches[i].grid.y, g[2] = launches[i].block.x; }
@@ -68,7 +69,7 @@ int hipLaunchKernel(const void* f, Dim3 g, Dim3 b, void**, size_t, void*) {
 int hipGetLastError() { const int e = last_error; last_error = 0; return e; }
 int hipGetDevice(int* d) { *d = 0; return 0; }
 int hipDeviceGetAttribute(int* v, int, int) { *v = 256; return 0; }
-int hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) { *n = 1; return 0; }
+int hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) { *n = occupancy; return 0; }
 int hipMalloc(void** p, size_t bytes) {
     if (bytes > malloc_limit) return last_error = kErrorMemory;
     *p = (void*)malloc_next;

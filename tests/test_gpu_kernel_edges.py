@@ -8,6 +8,7 @@ import torch
 import oracle
 import paper_2609_10264_amd as mvk
 import synth
+from tests.decode_forms import FORMS
 from tests.gpu_util import dev, host
 
 pytestmark = pytest.mark.gpu
@@ -127,6 +128,32 @@ def test_few_terms_few_columns(m, n, rx, ry, B, tx, ty, ell, inplace, p):
                                          vL=vL, vR=vR)
         assert np.array_equal(host(vL), vL0) and np.array_equal(host(vR), vR0)
         assert host(acc).tolist() == acc0.astype(np.uint32).tolist()
+        assert np.array_equal(host(Y), oracle.decode(PT, hyh, t.exi, t.exv, p=p))
+
+
+
+# Every form of decode_verify up to 16384 positions, each with an honest response
+# and one with the first column tampered.
+@pytest.mark.parametrize("m,ry,B,ell,ty,inplace,kernel", FORMS)
+@pytest.mark.parametrize("p", [synth.P, synth.P_BABYBEAR])
+def test_decode_forms(m, ry, B, ell, ty, inplace, kernel, p):
+    from tests.gpu_util import Instance
+    print("decode form", m, ry, B, ell, ty, inplace, kernel, p, flush=True)
+    t = Instance(580 + m + ty, m, 64, B, 2, 9, ty, ell, ry=ry, p=p).to_device()
+    mvk.keygen(t.key, t.dW)
+    PT, Q = host(t.key.PT), host(t.key.Q)
+    xh = mvk.encode(t.key, t.dX, t.dexi, t.dexv)
+    hyh = oracle.server_eval(t.W, host(xh), p=p)
+    for wrong in (0, 1):
+        hyh[0, m - 1] = (int(hyh[0, m - 1]) + wrong) % p
+        yh = dev(hyh)
+        vL = torch.empty((ell, B), dtype=torch.int32, device="cuda")
+        vR = torch.empty_like(vL)
+        Y, acc, _, _ = mvk.decode_verify(t.key, xh, yh, t.dexi, t.dexv, t.deyi, t.deyv, Y=yh if inplace else None,
+                                         vL=vL, vR=vR)
+        oacc, ovL, ovR = oracle.verify(t.cy, Q, host(xh), hyh, t.eyi, t.eyv, p=p)
+        assert host(acc).tolist() == oacc.astype(np.uint32).tolist() == [1 - wrong] + [1] * (B - 1)
+        assert np.array_equal(host(vL), ovL) and np.array_equal(host(vR), ovR)
         assert np.array_equal(host(Y), oracle.decode(PT, hyh, t.exi, t.exv, p=p))
 
 

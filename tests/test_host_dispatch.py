@@ -10,6 +10,8 @@ import sys
 
 import pytest
 
+from tests.decode_forms import FORMS
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 REC = os.path.join(HERE, "hip_record")
@@ -207,3 +209,33 @@ result["launches"] = launches()
     assert out["st"] == 0 and name.startswith("server_eval_mfma_dstat<%d, 1," % (2 if B <= 8 else 4)), name
     blocks = -(-m // 128)
     assert grid == -(-blocks // (8 // ks)) * 8
+
+
+@pytest.mark.parametrize("m,ry,B,ell,ty,inplace,kernel", FORMS)
+def test_decode_forms(host, m, ry, B, ell, ty, inplace, kernel):
+    # (a compute unit's LDS holds two workgroups of the second tile size, one of the larger ones)
+    out = host(f"""
+rec.rec_occupancy({2 if ry * m <= 8192 else 1})
+k = key({m}, 64, 2, {ry})
+ex, ey = sparse({B}, 9), sparse({ell}, {ty})
+yh = ptr()
+result["st"] = lib.mvk_decode_verify(ref(k), ptr(), yh, {B}, ref(ex), ref(ey), yh if {inplace} else ptr(), None, None,
+                                     ptr(), None)
+result["launches"] = launches()
+""")
+    assert out["st"] == 0
+    assert out["launches"][-1][0].startswith(kernel), out["launches"]
+
+
+# verify alone: the rule on many columns holds with r = 2 only
+@pytest.mark.parametrize("m,ry,B,ell,kernel", [(4096, 2, 16, 2, "decode_verify_syn<16, 4>"),
+                                               (4096, 2, 16, 3, "decode_verify_dot<16, 16>"),
+                                               (5000, 1, 16, 1, "decode_verify_dot<16, 16>")])
+def test_verify_forms(host, m, ry, B, ell, kernel):
+    out = host(f"""
+rec.rec_occupancy(2)
+k = key({m}, 64, 2, {ry})
+result["st"] = lib.mvk_verify(ref(k), ptr(), ptr(), {B}, ref(sparse({ell}, 31)), None, None, ptr(), None)
+result["launches"] = launches()
+""")
+    assert out["st"] == 0 and out["launches"][-1][0].startswith(kernel), out["launches"]
