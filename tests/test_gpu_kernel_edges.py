@@ -66,6 +66,22 @@ def test_keygen_segments(m, n, rx, ry, p):
     assert np.array_equal(host(key.Q), Q)
 
 
+
+# Long syndromes of dense vectors: one vector's segments on one XCD (six vectors and
+# more; an empty place at seven, vectors left over at 13), and four stripes a
+# workgroup (more than 2048 segments; a last one that is cut short).
+@pytest.mark.parametrize("k,r,count", [(4200, 4, 7), (8500, 2, 13), (8500, 2, 125), (20500, 1, 110)])
+@pytest.mark.parametrize("p", [synth.P, synth.P_BABYBEAR])
+def test_dense_syndromes_many_vectors(k, r, count, p):
+    from tests.gpu_util import code
+    print("dense syndromes", k, r, count, p, flush=True)
+    c = synth.raa_code(640 + k, k, r, p=p)
+    v = synth.field_uniform(641 + k, (count, k * r), p=p)
+    got = host(mvk.raa_syndrome(code(c, p), dev(v)))
+    for i in range(count):
+        assert np.array_equal(got[i], oracle.syn(c, v[i], p=p))
+
+
 # Preparations whose gathers take their own launch: many columns of a short
 # matrix, where items of 1024 columns would no longer need that launch; short
 # syndromes that join long ones (up to 256 of them, and one more); the gathers

@@ -239,3 +239,15 @@ result["st"] = lib.mvk_verify(ref(k), ptr(), ptr(), {B}, ref(sparse({ell}, 31)),
 result["launches"] = launches()
 """)
     assert out["st"] == 0 and out["launches"][-1][0].startswith(kernel), out["launches"]
+
+
+# More segments than the chip holds workgroups: four stripes each, also of dense
+# vectors (the sizes of the GPU test).
+@pytest.mark.parametrize("k,r,count,stripes", [(8500, 2, 13, 1), (8500, 2, 120, 1), (8500, 2, 125, 4), (20500, 1, 110, 4)])
+def test_dense_stripes(host, k, r, count, stripes):
+    out = host(f"""
+result["st"] = lib.mvk_raa_syndrome(ref(code({k}, {r})), ptr(), {count}, ptr(), None)
+result["launches"] = launches()
+""")
+    assert out["st"] == 0
+    assert [l[0] for l in out["launches"][1:]] == [f"syn_p1<false, {stripes}>", f"syn_p2<{stripes}>", "syn_p3"]
