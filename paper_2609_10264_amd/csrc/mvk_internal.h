@@ -21,6 +21,9 @@ struct ServerEvalPlan {
 // rows_aligned: row-major W holds whole 16-byte granules (n a multiple of 16, W
 // 16-byte aligned); packed W always does.
 ServerEvalPlan server_eval_plan(uint32_t m, uint32_t n, uint32_t B, int path, bool packed, bool rows_aligned = true);
+// Launches, each of which reads W, of a row-major product with B queries whose rows
+// are not whole aligned 16-byte granules.
+uint32_t server_any_launches(uint32_t m, uint32_t n, uint32_t B);
 // W: row-major m x n, or (packed) the layout written by launch_pack_w.
 hipError_t launch_server_eval(const int8_t* W, uint32_t m, uint32_t n, const uint32_t* X, uint32_t B,
                               uint32_t* Y, int path, bool packed, void* ws, uint32_t* counters, hipStream_t s);

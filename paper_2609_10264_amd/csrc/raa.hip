@@ -601,12 +601,18 @@ size_t encT_seg_words(size_t N, size_t nvec) {
 // 4096).  It pays where t3 no longer fits the memory-side cache: 2048 x 2048, r
 // = 3 (t3 of 50 MB) takes 174 us against 152 on the three-pass form, 4096 x
 // 4096 (201 MB) 341 to 380 against 416 to 431; with M's rows not whole aligned
-// granules the product takes four launches (4095 x 4097: 561 us against 517).
+// granules the product takes four launches (4095 x 4097: 561 us against 517),
+// eight for rows above 16384 and sixteen above 32768.  A launch costs about 0.5
+// us per million entries of M, and the passes saved 2.8 us per million positions,
+// r times as many: up to 4 r launches (2051 x 65537, r = 1, sixteen: 3496 us against
+// 1707; 2051 x 33001, r = 3, sixteen: 2378 against 2129; 4099 x 30001, r = 1,
+// eight: 1634 against 1375; 2051 x 20001, r = 3, eight: 1245 against 1542).
 // Fewer vectors than 2048 make too few workgroups (11008 x 256: 306 us against
 // 178 with 128 segments).
 namespace {
 constexpr uint32_t kEncSegs = 32;
 constexpr size_t kEncSegsAbove = (size_t)192 << 20, kEncSegsAboveAny = (size_t)400 << 20;  // bytes of t3
+constexpr uint32_t kEncReadings = 4;  // readings of M per r
 struct EncPlan {
     uint32_t nseg, L, nq, ntile, npad;  // npad: positions the passes read (whole segments, two more steps)
     size_t o_pos, o_row1, o_row2, o_c1, o_c1off, o_c2, o_idx, o_val, o_qry, o_off, o_syn, o_srv, o_t3, bytes;
@@ -621,6 +627,7 @@ bool enc_i8_plan(uint32_t k, uint32_t r, uint32_t nvec, bool rows_aligned, EncPl
     p.L = (uint32_t)((N + kEncSegs * unit - 1) / (kEncSegs * unit) * unit);
     p.nseg = (uint32_t)((N + p.L - 1) / p.L);
     p.nq = p.nseg - 1;
+    if (!rows_aligned && server_any_launches(nvec, k, 2 * p.nq) > kEncReadings * r) return false;
     p.srv = server_eval_plan(nvec, k, 2 * p.nq, MVK_PATH_AUTO, false, rows_aligned);
     size_t b = 0;
     auto take = [&](size_t bytes) {

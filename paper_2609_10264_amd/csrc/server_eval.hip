@@ -1390,6 +1390,12 @@ uint32_t any_group(uint32_t m, uint32_t n, uint32_t left) {
 }
 }  // namespace
 
+uint32_t server_any_launches(uint32_t m, uint32_t n, uint32_t B) {
+    uint32_t c = 0;
+    for (uint32_t left = B; left; ++c) left -= any_group(m, n, left);
+    return c;
+}
+
 ServerEvalPlan server_eval_plan(uint32_t m, uint32_t n, uint32_t B, int path, bool packed, bool rows_aligned) {
     ServerEvalPlan pl{0, 0};
     if (path == MVK_PATH_VALU || B <= 4 || (!packed && (size_t)m * n < 16)) return pl;

@@ -251,3 +251,23 @@ result["launches"] = launches()
 """)
     assert out["st"] == 0
     assert [l[0] for l in out["launches"][1:]] == [f"syn_p1<false, {stripes}>", f"syn_p2<{stripes}>", "syn_p3"]
+
+
+# keygen with rows that are not whole 16-byte granules: the offsets of the segments
+# are a product that reads the matrix once for 16, 8 or 4 of its 62 queries
+# (rows up to 16384, 32768 and above), which pays up to 4 r readings.
+@pytest.mark.parametrize("m,n,r,forms", [
+    (2051, 65537, 1, ["enc_pass2"]), (2051, 33001, 2, ["enc_pass2", "enc_seg<false>"]), (2051, 33001, 4, ["enc_seg<false>"]),
+    (4099, 30001, 1, ["enc_pass2", "enc_seg<false>"]), (2051, 30001, 2, ["enc_seg<false>"]),
+    (40001, 3001, 1, ["enc_pass2"]), (40001, 3001, 2, ["enc_seg<false>", "enc_pass2"]), (2051, 131056, 2, ["enc_seg<false>"]),
+])
+def test_keygen_long_ragged_rows(host, m, n, r, forms):
+    out = host(f"""
+k = key({m}, {n}, {r}, {r})
+result["st"] = lib.mvk_keygen(ref(k), ptr(), None)
+result["launches"] = launches()
+""")
+    assert out["st"] == 0
+    names = [n for n, _, _ in out["launches"] if n.startswith(("enc_pass2", "enc_seg<false>"))]
+    names = ["enc_pass2" if n.startswith("enc_pass2") else n for n in names]
+    assert [n for i, n in enumerate(names) if names[i - 1:i] != [n]] == forms
