@@ -209,22 +209,52 @@ inline YOut yout_shift(YOut o, uint32_t b0) {
 typedef int32_t v4i_b __attribute__((ext_vector_type(4), aligned(1)));
 typedef uint32_t v4u_w __attribute__((ext_vector_type(4), aligned(4)));
 
-// The 16 query elements k0 .. k0+15 of row xr (n elements, zero beyond them
-// and where !ok), in whole words at any word alignment.
+// Query elements k .. k+3 of row xr (n >= 4 elements) in one load at any word
+// alignment.  Where they run past the row the load is moved down to its last
+// four, without a branch: x4_back elements too far (0 where none are, more than 3
+// where all four lie past the row).  Only the waves that hold the end of a row
+// move them back (x4_shift).  Packed W, 28000 x 146, one query: 9.1 us, against
+// 9.3 word by word and 10.6 with the words of the row's end in a branch of
+// their own; 8000 x 9001: 14.9, 16.5 and 15.7 us.
+__device__ __forceinline__ v4u_w load_x4(const uint32_t* xr, uint32_t k, uint32_t n) {
+    return *reinterpret_cast<const v4u_w*>(xr + (k + 4 <= n ? k : n - 4));
+}
+__device__ __forceinline__ uint32_t x4_back(uint32_t k, uint32_t n) { return k + 4 <= n ? 0u : k + 4 - n; }
+// Element e + back of x as element e, zero beyond the fourth (back <= 3).
+__device__ __forceinline__ void x4_shift(uint32_t* x, uint32_t back) {
+    const bool one = back & 1u, two = back & 2u;
+    const uint32_t a0 = one ? x[1] : x[0], a1 = one ? x[2] : x[1], a2 = one ? x[3] : x[2], a3 = one ? 0u : x[3];
+    x[0] = two ? a2 : a0;
+    x[1] = two ? a3 : a1;
+    x[2] = two ? 0u : a2;
+    x[3] = two ? 0u : a3;
+}
+
+// The 16 query elements k0 .. k0+15 (k0 a multiple of 16) of row xr (n elements,
+// zero beyond them and where !ok), in whole words at any word alignment.
 __device__ __forceinline__ void load_x16(uint32_t (&x)[16], const uint32_t* xr, uint32_t k0, uint32_t n, bool ok) {
-    if (ok && k0 + 16 <= n) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const v4u_w t = *reinterpret_cast<const v4u_w*>(xr + k0 + 4 * v);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) x[4 * v + e] = t[e];
-        }
-    } else {
+    if (n < 4) {  // (uniform)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-            const bool in = ok && k0 + e < n;
-            const uint32_t t = xr[in ? k0 + e : 0u];
+            const bool in = e < 4 && ok && k0 + e < n;
+            const uint32_t t = e < 4 ? xr[in ? e : 0] : 0u;
             x[e] = in ? t : 0u;
+        }
+        return;
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const bool in = ok && k0 + 4 * v < n;
+        const v4u_w t = load_x4(xr, k0 + 4 * v, n);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[4 * v + e] = in ? t[e] : 0u;
+    }
+    // the four that hold the end of the row
+    if (n % 4 != 0 && __any(ok && k0 < n && n < k0 + 16)) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const uint32_t back = x4_back(k0 + 4 * v, n);
+            x4_shift(x + 4 * v, back < 4 ? back : 0u);
         }
     }
 }
@@ -287,8 +317,11 @@ __device__ __forceinline__ v4i w16_at(v4i w, size_t off, size_t total) {
 // neighbouring k-blocks (64 of a line's 128 bytes each), which at any alignment
 // are not read with the non-temporal hint.
 enum WLayout { kWRowVec = 0, kWRowAny = 1, kWPacked = 2 };
+// Query loads of the small kernel: 16 bytes at a time (rows of whole 16-byte
+// granules, 16-byte aligned), four words at any word (load_x4), or word by word.
+enum XLoad { kXWords = 0, kXVec = 1, kXAny = 2 };
 
-template <int QB, int KW, int KBW, bool VEC, int WL>
+template <int QB, int KW, int KBW, int XL, int WL>
 __global__ __launch_bounds__(KW * 64) void server_eval_mfma_small(const int8_t* __restrict__ W, uint32_t m,
                                                                   uint32_t n, const uint32_t* __restrict__ X,
                                                                   uint32_t B, const YOut Y) {
@@ -328,27 +361,26 @@ __global__ __launch_bounds__(KW * 64) void server_eval_mfma_small(const int8_t* 
             const uint32_t k = kc0 + 4 * k4;
             const bool okq = q0 + q < B;
             const uint32_t* xr = X + (size_t)(okq ? q0 + q : 0) * n;
-            if (VEC) {
+            if (XL == kXVec) {
                 const uint4 t = *reinterpret_cast<const uint4*>(xr + (k < n ? k : 0));
                 xok[it] = (okq && k < n) ? 0xfu : 0u;
                 xq[it][0] = t.x;
                 xq[it][1] = t.y;
                 xq[it][2] = t.z;
                 xq[it][3] = t.w;
+            } else if (XL == kXAny) {
+                const v4u_w t = load_x4(xr, k, n);
+                const uint32_t back = x4_back(k, n);
+                xok[it] = okq && back < 4 ? 0xfu >> back : 0u;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) xq[it][e] = t[e];
             } else {
-                if (k + 4 <= n) {
-                    const v4u_w t = *reinterpret_cast<const v4u_w*>(xr + k);
-                    xok[it] = okq ? 0xfu : 0u;
+                xok[it] = 0u;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) xq[it][e] = t[e];
-                } else {  // the end of the row
-                    xok[it] = 0u;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const bool ok = okq && k + e < n;
-                        xok[it] |= ok ? (1u << e) : 0u;
-                        xq[it][e] = xr[ok ? k + e : 0];
-                    }
+                for (int e = 0; e < 4; ++e) {
+                    const bool ok = okq && k + e < n;
+                    xok[it] |= ok ? (1u << e) : 0u;
+                    xq[it][e] = xr[ok ? k + e : 0];
                 }
             }
         }
@@ -389,12 +421,18 @@ __global__ __launch_bounds__(KW * 64) void server_eval_mfma_small(const int8_t* 
             const int q = idx / (KC / 4);
             const int k4 = idx % (KC / 4);
             int32_t p[4];
+            if (XL == kXAny) {
+                const uint32_t back = x4_back(kc0 + 4 * k4, n);  // (above 3: masked)
+                if (__any(back - 1 < 3)) x4_shift(xq[it], back);
+            }
             const uint32_t x0 = (xok[it] & 1u) ? xq[it][0] : 0u, x1 = (xok[it] & 2u) ? xq[it][1] : 0u;
             const uint32_t x2 = (xok[it] & 4u) ? xq[it][2] : 0u, x3 = (xok[it] & 8u) ? xq[it][3] : 0u;
             digit_planes(x0, x1, x2, x3, p[0], p[1], p[2], p[3]);
 #pragma unroll
             for (int d = 0; d < 4; ++d) *reinterpret_cast<int32_t*>(dig + (q * 4 + d) * STRIDE + 4 * k4) = p[d];
         }
+        // (else the masks of W, and the waits for it, move up before the conversion)
+        if (XL == kXAny) __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
         // Blocks past the end of the row hold zeros on both operands and add
         // nothing, so every MFMA runs unconditionally.
@@ -453,12 +491,15 @@ hipError_t launch_mfma_small(const int8_t* W, uint32_t m, uint32_t n, const uint
 #define MVK_SMALL(XV, WLV) \
     hipLaunchKernelGGL((server_eval_mfma_small<QB, KW, KBW, XV, WLV>), grid, dim3(KW * 64), 0, s, W, m, n, X, B, Y)
     if (packed) {
-        if (xvec) MVK_SMALL(true, kWPacked);
-        else MVK_SMALL(false, kWPacked);
+        if (xvec) MVK_SMALL(kXVec, kWPacked);
+        else if (n >= 4) MVK_SMALL(kXAny, kWPacked);
+        else MVK_SMALL(kXWords, kWPacked);
     } else if (xvec && wvec) {
-        MVK_SMALL(true, kWRowVec);
+        MVK_SMALL(kXVec, kWRowVec);
+    } else if (n >= 4) {
+        MVK_SMALL(kXAny, kWRowAny);
     } else {
-        MVK_SMALL(false, kWRowAny);
+        MVK_SMALL(kXWords, kWRowAny);
     }
 #undef MVK_SMALL
     return hipGetLastError();

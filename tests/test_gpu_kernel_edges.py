@@ -48,6 +48,25 @@ def test_query_alignment(m, n, B):
         assert np.array_equal(host(mvk.server_eval(mvk.pack_weights(dev(W)), dX)), oracle.server_eval(W, X))
 
 
+
+# The end of a query row in the wide loads of X: rows of fewer than four elements, of
+# every remainder by four and by sixteen, and the last row at the end of its buffer.
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 6, 7, 15, 17, 18, 31, 63, 65, 130, 179, 999, 4097, 4102])
+@pytest.mark.parametrize("B", [1, 2, 3, 4, 7, 12, 16, 20, 40])
+def test_query_row_ends(n, B):
+    m = 37
+    W = synth.weights(530 + n, m, n, lo=-128)
+    X = synth.field_uniform(531 + B + n, (B, n))
+    print("row ends", n, B, flush=True)
+    want = oracle.server_eval(W, X)
+    buf = torch.full((B * n + 8,), -1, dtype=torch.int32, device="cuda")  # (what a read past a row would bring in)
+    for off in (0, 5):
+        dX = buf[off:off + B * n].view(B, n)
+        dX.copy_(dev(X))
+        for dW in (dev(W), mvk.pack_weights(dev(W))):
+            assert np.array_equal(host(mvk.server_eval(dW, dX)), want)
+
+
 # keygen with the segment offsets from one server product (at least 2048 vectors
 # and 192 MB of intermediate sums, 400 MB where the matrix rows are not whole
 # 16-byte granules): the fewest vectors, both encodings; an odd number of
