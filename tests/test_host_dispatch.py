@@ -271,3 +271,19 @@ result["launches"] = launches()
     names = [n for n, _, _ in out["launches"] if n.startswith(("enc_pass2", "enc_seg<false>"))]
     names = ["enc_pass2" if n.startswith("enc_pass2") else n for n in names]
     assert [n for i, n in enumerate(names) if names[i - 1:i] != [n]] == forms
+
+
+# Long syndromes placed by XCD (whole eights and a rest of six or more; grid.y counts
+# the empty places): vectors of one length, not 20 short ones with two long ones
+# that two XCDs would have to take by themselves.
+@pytest.mark.parametrize("m,n,ry,B,ell,rows", [(64, 9000, 2, 22, 0, 24), (64, 9000, 2, 21, 0, 21), (17152, 81, 4, 20, 2, 22),
+                                               (17152, 81, 4, 6, 16, 24), (9000, 17152, 2, 20, 2, 24)])
+def test_placement_by_xcd(host, m, n, ry, B, ell, rows):
+    out = host(f"""
+k = key({m}, {n}, 2, {ry})
+ex, ey = sparse({B}, 8), sparse({ell}, 8)
+result["st"] = lib.mvk_client_prepare(ref(k), ref(ex), ref(ey) if {ell} else None, ptr(), ptr(), ptr(), ptr(), None, 0, None)
+result["launches"] = launches()
+""")
+    assert out["st"] == 0
+    assert [l[2] for l in out["launches"] if l[0].startswith("syn_p1")] == [rows], out["launches"]
