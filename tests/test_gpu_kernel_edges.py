@@ -105,10 +105,12 @@ def test_dense_syndromes_many_vectors(k, r, count, p):
 # matrix, where items of 1024 columns would no longer need that launch; short
 # syndromes that join long ones (up to 256 of them, and one more); the gathers
 # beside the second pass of long ones (one stripe per workgroup), by items of 64,
-# 256 and 1024 columns; four stripes.
+# 256 and 1024 columns; four stripes.  (With 16400 rows the joined grid would be
+# mostly empty, with 8500 not.)
 @pytest.mark.parametrize("m,n,rx,ry,B,tx", [(1024, 64, 2, 2, 300, 8), (8192, 300, 3, 3, 40, 20), (4352, 6000, 3, 2, 62, 70),
                                             (16400, 64, 2, 2, 254, 8), (16400, 64, 2, 2, 260, 8),
-                                            (8191, 300, 3, 3, 40, 20), (1100, 8200, 2, 2, 220, 8)])
+                                            (8191, 300, 3, 3, 40, 20), (1100, 8200, 2, 2, 220, 8),
+                                            (8500, 64, 2, 2, 254, 8), (8500, 64, 2, 2, 257, 8)])
 @pytest.mark.parametrize("p", [synth.P, synth.P_BABYBEAR])
 def test_prepare_split(m, n, rx, ry, B, tx, p):
     from tests.gpu_util import Instance

@@ -287,3 +287,18 @@ result["launches"] = launches()
 """)
     assert out["st"] == 0
     assert [l[2] for l in out["launches"] if l[0].startswith("syn_p1")] == [rows], out["launches"]
+
+
+# ... nor where the longest vector would leave most of the joined grid empty
+@pytest.mark.parametrize("m,n,rx,ry,B,ell,join", [(23168, 563, 4, 8, 37, 2, False), (13248, 1212, 1, 8, 42, 4, True),
+                                                     (8500, 64, 2, 2, 254, 2, True), (8500, 64, 2, 2, 257, 2, False),
+                                                     (16400, 64, 2, 2, 254, 2, False)])
+def test_prepare_join_of_uneven_lengths(host, m, n, rx, ry, B, ell, join):
+    out = host(f"""
+k = key({m}, {n}, {rx}, {ry})
+ex, ey = sparse({B}, 8), sparse({ell}, 8)
+result["st"] = lib.mvk_client_prepare(ref(k), ref(ex), ref(ey), ptr(), ptr(), ptr(), ptr(), None, 0, None)
+result["launches"] = launches()
+""")
+    assert out["st"] == 0
+    assert any(l[0].startswith("client_prepare_kernel") for l in out["launches"]) == (not join), out["launches"]
