@@ -34,8 +34,7 @@ __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
 }
 
 // Sums of K values per thread over the workgroup, sum i added into acc[i]
-// (64-bit atomics: exact, so the order of the additions does not matter; null:
-// not wanted).
+// (64-bit atomics: exact, so the order of the additions does not matter).
 template <int K>
 __device__ __forceinline__ void block_add(const uint64_t (&v)[K], uint64_t (*red)[4], unsigned long long* const (&acc)[K]) {
     static_assert(K <= 4, "red holds four sums per wave");
@@ -48,7 +47,7 @@ __device__ __forceinline__ void block_add(const uint64_t (&v)[K], uint64_t (*red
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < K; ++i)
-        if (threadIdx.x == (uint32_t)i && acc[i]) {
+        if (threadIdx.x == (uint32_t)i) {
             uint64_t t = 0;
 #pragma unroll
             for (int w = 0; w < kBW; ++w) t += red[w][i];
@@ -91,8 +90,11 @@ __global__ __launch_bounds__(kBT) void batch_check_kernel(CheckArgs a) {
         for (uint32_t q = 0; q < a.ell; q += 2) {
             const uint32_t q1 = q + 1 < a.ell ? q + 1 : q;
             const uint32_t u0 = a.Ut[(size_t)q * Bn + (size_t)b * a.n + ks], u1 = a.Ut[(size_t)q1 * Bn + (size_t)b * a.n + ks];
-            block_add<2>({ffold((uint64_t)u0 * x), ffold((uint64_t)u1 * x)}, red,
-                         {&a.accL[(size_t)q * a.B + b], q1 > q ? &a.accL[(size_t)q1 * a.B + b] : nullptr});
+            unsigned long long* s0 = &a.accL[(size_t)q * a.B + b];
+            if (q1 > q)
+                block_add<2>({ffold((uint64_t)u0 * x), ffold((uint64_t)u1 * x)}, red, {s0, s0 + a.B});
+            else
+                block_add<1>({ffold((uint64_t)u0 * x)}, red, {s0});
         }
     } else if (bid < nL + nR) {
         const uint32_t w = bid - nL;
@@ -103,8 +105,11 @@ __global__ __launch_bounds__(kBT) void batch_check_kernel(CheckArgs a) {
         for (uint32_t q = 0; q < a.ell; q += 2) {
             const uint32_t q1 = q + 1 < a.ell ? q + 1 : q;
             const uint32_t r0 = a.R[(size_t)q * a.m + is], r1 = a.R[(size_t)q1 * a.m + is];
-            block_add<2>({ffold((uint64_t)r0 * y), ffold((uint64_t)r1 * y)}, red,
-                         {&a.accR[(size_t)q * a.B + b], q1 > q ? &a.accR[(size_t)q1 * a.B + b] : nullptr});
+            unsigned long long* s0 = &a.accR[(size_t)q * a.B + b];
+            if (q1 > q)
+                block_add<2>({ffold((uint64_t)r0 * y), ffold((uint64_t)r1 * y)}, red, {s0, s0 + a.B});
+            else
+                block_add<1>({ffold((uint64_t)r0 * y)}, red, {s0});
         }
     } else if (bid < nL + nR + a.nbS) {
         const uint32_t c = (bid - nL - nR) * kBT + tid;
@@ -120,11 +125,18 @@ __global__ __launch_bounds__(kBT) void batch_check_kernel(CheckArgs a) {
                     uq[i] = act ? a.Ut[(size_t)(i && q1 ? q + 1 : q) * Bn + cs] : 0u;
                 }
                 unsigned long long* s0 = &a.accS[(size_t)q * a.ell2 + j];
-                block_add<4>({ffold((uint64_t)rj[0] * uq[0]), ffold((uint64_t)rj[1] * uq[0]),
-                              ffold((uint64_t)rj[0] * uq[1]), ffold((uint64_t)rj[1] * uq[1])},
-                             red,
-                             {s0, j1 ? s0 + 1 : nullptr, q1 ? s0 + a.ell2 : nullptr,
-                              q1 && j1 ? s0 + a.ell2 + 1 : nullptr});
+                // (a single row or column of sums: no work for the missing ones)
+                const uint64_t s00 = ffold((uint64_t)rj[0] * uq[0]);
+                if (j1 && q1)
+                    block_add<4>({s00, ffold((uint64_t)rj[1] * uq[0]), ffold((uint64_t)rj[0] * uq[1]),
+                                  ffold((uint64_t)rj[1] * uq[1])},
+                                 red, {s0, s0 + 1, s0 + a.ell2, s0 + a.ell2 + 1});
+                else if (j1)
+                    block_add<2>({s00, ffold((uint64_t)rj[1] * uq[0])}, red, {s0, s0 + 1});
+                else if (q1)
+                    block_add<2>({s00, ffold((uint64_t)rj[0] * uq[1])}, red, {s0, s0 + a.ell2});
+                else
+                    block_add<1>({s00}, red, {s0});
             }
     } else {
         // one (q, j) pair per workgroup; the t x t' lookups kLook per thread
