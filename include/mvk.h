@@ -307,8 +307,11 @@ mvk_status mvk_decode_verify_prepared(const mvk_key *key, const uint32_t *Xhat,
  *       U  : device, ell x n, written, U_q = e_q^T Q
  * The outputs are secret to the client (they determine e); the challenges
  * never leave the client, so they may be drawn before the responses exist.
- * One launch when Nx and Ny are at most 16384 (syndromes and row gathers side
- * by side), else the longer syndromes run first in their own launches.
+ * One launch when Nx and Ny are at most 16384 and the row gathers are few
+ * (syndromes and gathers side by side).  Else the gathers take a launch of their
+ * own; longer syndromes run by segments over several launches, the second of
+ * which may be that of the gathers, and shorter ones in a launch of their own
+ * or with the longer ones.
  * done_flag (device word, may be NULL): set to done_value (!= 0) once every
  *   output is stored and visible device-wide, as mvk_flag_signal would after
  *   the call, but without a launch of its own.
@@ -324,9 +327,9 @@ mvk_status mvk_client_prepare(const mvk_key *key, const mvk_sparse *ex, const mv
  * cx arrays), so that the noise vectors ex and the input mask Mx are shared;
  * My[g] = P_g e_b, R[g] = Gy_g e_q and U[g] = e_q^T Q_g for each key with its
  * own challenges ey[g] (the same count and t for every g).  My, R, U, ey: host
- * arrays of G pointers (device buffers as mvk_client_prepare).  One launch
- * when Nx and Ny are at most 16384 (else the longer syndromes first, in their
- * own launches); same outputs, bit for bit, as G calls of mvk_client_prepare.
+ * arrays of G pointers (device buffers as mvk_client_prepare).  Launches as
+ * mvk_client_prepare, for all G keys at once; same outputs, bit for bit, as G
+ * calls of mvk_client_prepare.
  * Errors: as mvk_client_prepare, plus MVK_EINVAL (G out of range, keys of
  * different shapes or privacy codes, challenge sets of different sizes).
  */
@@ -338,8 +341,8 @@ mvk_status mvk_client_prepare_group(uint32_t G, const mvk_key *const *keys, cons
 /*
  * Client preparation of several inputs and the keys they feed in one call
  * (for example the four inputs and seven projections of a decoder layer):
- * every syndrome of block length at most 16384 and every row gather of the
- * call run in one launch, instead of one launch per input.
+ * every syndrome and every row gather of the call share the launches of one
+ * mvk_client_prepare.
  *   G    : 1..MVK_MAX_PREP keys; keys, ex, ey, Mx, My, R, U: host arrays of G
  *          entries (ex, ey, done_flags may also be NULL as a whole)
  *   ex[g]: noise of key g's input (NULL or count 0: no masks for key g).

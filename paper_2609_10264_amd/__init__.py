@@ -344,8 +344,8 @@ def client_prepare_group(keys: list, ex_idx: torch.Tensor, ex_val: torch.Tensor,
 
 def client_prepare_multi(keys: list, exs: list, eys: list, outs: list | None = None, done_flags: list | None = None,
                          done_value: int = 1, stream=None) -> list:
-    """client_prepare for several keys and inputs in one call (one launch for
-    the short syndromes and every row gather).  exs[g] = (ex_idx, ex_val) of
+    """client_prepare for several keys and inputs in one call (they share the
+    launches of one client_prepare).  exs[g] = (ex_idx, ex_val) of
     key g's input, or None; eys[g] = (ey_idx, ey_val) or None.  Keys listed
     with the same noise tensors share their input: the input mask is computed
     once and every Prepared of that input holds the same Mx tensor.

@@ -74,7 +74,9 @@ struct CheckArgs {
 // clears them and writes the results and the accept bits.
 //
 // Bound by latency: what a workgroup adds up at once is loaded at once, two
-// repetitions (and, of the secondary right sides, two by two) a time, and the
+// repetitions (and, of the secondary right sides, two by two) a time (an odd last
+// one alone: 6790 x 128, two claims, 1 and 16 repetitions, 28.7 us a call against
+// 33.1 with an empty second one), and the
 // last workgroup takes every accumulator with a thread of its own.
 __global__ __launch_bounds__(kBT) void batch_check_kernel(CheckArgs a) {
     __shared__ uint64_t red[kBW][4];

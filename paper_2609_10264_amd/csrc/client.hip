@@ -497,6 +497,7 @@ __global__ __launch_bounds__(kFusedThreads) void decode_verify_syn(
 // no scatter by Pi1, no fold, and nobody waits for a whole r_q.  The price is r
 // times as many products with Yhat, gathered, which is why this is for few
 // columns.  Short blocks, where it takes the place of a whole syndrome: up to 16
+// (fewer where decode_verify_syn does well with them, dv_dot_fits)
 // columns (two repetitions, 4096 x 4096, r = 3: 14.6 us against 23.9 with 8
 // columns, 18.6 against 25.0 with 16), up to 8 where the syndrome is of 4096
 // positions at most (256 x 256, r = 2: 8.4 us against 10.1 with 8, 11.2 against
@@ -565,9 +566,9 @@ struct TermSums {
 // (from the sorted terms, ty <= kSortMax) and its products with V2 at all N
 // positions: those that Pi2 sends into the segment go to LDS, those that it
 // sends behind it are added up to the segment's carry.  That repeats N
-// products per workgroup (by instruction count about
-// 1 us of one CU at N = 12288) and takes the place
-// of a scan and two scatters of the whole block by one CU (about 10 us).
+// products per workgroup and takes the place of a scan and two scatters of the
+// whole block by one CU: 11.4 us for the launch at N = 12288 (4096 x 4096, r = 3,
+// one column, two repetitions), where decode_verify_syn took 18.0.
 constexpr uint32_t kSortMax = 64;
 template <int MB>
 struct DotLds {

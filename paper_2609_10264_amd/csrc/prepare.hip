@@ -320,9 +320,10 @@ __global__ __launch_bounds__(kPrepThreads) void client_prepare_kernel(PrepArgs a
 // The gathers of a preparation launch alone, one item per 256-thread
 // workgroup (a quarter of client_prepare_kernel's), for launches with many
 // items: small workgroups with a small LDS footprint share compute units with
-// the kernels of other streams instead of taking whole ones.  The syndromes
+// the kernels of other streams instead of taking whole ones.  The short syndromes
 // then run before, in client_prepare_kernel launched with their workgroups
-// only.  SIG as in client_prepare_kernel.
+// only, or by segments with the long ones (PrepPlan::join).  SIG as in
+// client_prepare_kernel.
 constexpr size_t gather_part_of(bool vec, bool wide) { return wide ? gather_part_wide() : gather_part(vec); }
 template <bool SIG, bool VEC, bool WIDE>
 __device__ __forceinline__ void gather_role(const PrepArgs& a, uint32_t item, uint64_t* part) {

@@ -5,17 +5,21 @@
 //   syndrome  G v   = R Pi1 V1 A Pi2 V2 A v             (suffix sum, scale,
 //             scatter by pi2, suffix sum, scale, scatter by pi1, fold r)
 //
-// Two kernel shapes:
+// Kernel shapes:
 //  * enc_pass1/2: many vectors at once (Preprocess encodes every row and every
 //    column of W).  One lane owns one vector within a segment of positions, so
 //    each prefix sum is a running sum per lane plus a scan over segments, and
 //    every access to the batch (vector index innermost) is a coalesced row.
 //    The code arrays are indexed by the position only, which is uniform across
 //    the workgroup, so they come through scalar loads.
+//  * enc_seg: the same for many vectors of an int8 matrix (from 2048 vectors and
+//    192 MB of intermediate sums on), the value of both prefix sums before every
+//    segment from one server product in place of the passes that add up segments.
 //  * syn_wg: few vectors (Encrypt: one per query column; Verify: one per
 //    repetition) of length up to 16384.  One 1024-thread workgroup owns one
 //    vector; both work arrays stay in LDS.
-//  * syn_p1/p2/p3: longer vectors, cut into segments over three launches.
+//  * syn_p1/p2/p3: longer vectors (and shorter ones that go with them), cut into
+//    segments over three launches.
 #include "field.h"
 #include "mvk_internal.h"
 #include "syn_block.h"
@@ -312,7 +316,9 @@ __global__ __launch_bounds__(256) void enc_dq(uint32_t k, uint32_t r, uint32_t N
 // keygen 803 us.  t3 and the output are streamed with the non-temporal hint (950
 // us without it); t3 kept for chunks of 36 to 256 MB of vectors, to stay in the
 // memory-side cache between its write and its read, measured 890 to 1180 us:
-// each launch then has too few workgroups.
+// each launch then has too few workgroups.  The BabyBear build's second sum keeps
+// 15 registers in scratch (128 is what four waves per SIMD leave) and is bound by
+// HBM all the same: 4.3 GB in 774 us, 5.5 TB/s (8192 x 8192, r = 8).
 struct SegIdx {
     uint32_t row[kSegRows];
 };
@@ -431,9 +437,12 @@ __global__ __launch_bounds__(kSynThreads) void syn_wg(uint32_t k, uint32_t r, co
 }
 
 // ---------------------------------------------------------------------------
-// Multi-workgroup syndrome for long blocks (several workgroups per vector).
-// The length-N work array is cut into segments of kSegLen positions, one
-// workgroup each, in three launches:
+// Multi-workgroup syndrome (several workgroups per vector).  The length-N work array
+// is cut into segments, one workgroup each, of kSegLen positions or, with four
+// stripes (seg_shape), of four times as many, in three launches; the second may
+// run beside the row gathers of a preparation (prepare.hip), and the
+// decode/verify of long blocks has its own first and second launch with the same
+// parts (client.hip):
 //   p1: a = suffix sum of the input (the carry into a segment is the sum of the
 //       input beyond it: for sparse input a sum over the t terms, for dense
 //       input a reduction of the tail), then b[pi2[j]] = v2[j] a[j]; p1 also

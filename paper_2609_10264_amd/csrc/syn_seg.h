@@ -1,6 +1,7 @@
-// The two scans of a syndrome over segments of a long block (raa.hip, p1 and
-// p2), as the part of one workgroup of kSegThreads threads: shared by the
-// syndrome launches and the decode/verify of long blocks.
+// The two scans of a syndrome by segments (raa.hip, p1 and p2), as the part of one
+// workgroup of kSegThreads threads: shared by the syndrome launches, the gather
+// launch that holds the second one (prepare.hip) and the decode/verify of long
+// blocks (client.hip).
 #pragma once
 #include "field.h"
 #include "mvk_internal.h"
@@ -45,7 +46,7 @@ __device__ __forceinline__ uint64_t block_sum_u64_256(uint64_t v, uint64_t* red)
 // so that every access of four words is coalesced.  A segment costs its
 // workgroup a chain of dependent memory accesses (ticket, loads, publication,
 // look-back) of about 7 us whatever its length; with many vectors four stripes
-// pay it for a quarter of the workgroups (seg_stripes).
+// pay it for a quarter of the workgroups (seg_shape).
 //
 // kSegPer consecutive words from position j on (those from `end` on read
 // position `end` - 1; j may lie past it).
@@ -100,9 +101,9 @@ struct SegSet {
     uint32_t* work;
     uint32_t k, r, t, count;
 };
-// Several syndromes of long blocks share each of the three launches: set i is
-// count vectors over its own code, with its own work region (count x 2N words
-// and the look-back state).  grid.y runs over the vectors of all sets, grid.x
+// Several syndromes share each of the launches (long blocks, and short ones that
+// join them): set i is count vectors over its own code, with its own work region
+// (count x 2N words and the look-back state).  grid.y runs over the vectors of all sets, grid.x
 // over the segments (p1, p2) or the fold chunks (p3) of the longest; the
 // workgroups past a shorter set's end return at once (before p2's ticket).
 struct SegArgs {
