@@ -1363,12 +1363,13 @@ bool dv_dot_fits(const mvk_key& key, uint32_t B, uint32_t ell, uint32_t ty, cons
     // against 14.7).  Without Y the dot form has no decode role and is as fast or
     // faster with r = 1 (5000 x 3000, 16 columns: 13.9 and 14.0 with one, 15.3
     // against 14.6 with two), not with r = 2 (4096 x 4096: 13.4 against 15.4).
-    // With one column a lane the dot form keeps all of its range (one repetition
-    // and 16 columns are even: 14.1 and 13.1 us at 520 x 512, r = 8, 13.8 and 14.1
-    // at 1366 x 4096, r = 3, 15.7 and 16.2 at 1000 x 16000, r = 8).
-    if ((Y || key.cy.r > 1) && Ny <= kDotFewCols && B >= 10 + 3 * ell &&
-        dv_decode_cols(key.m, B, key.PT, Yhat, Y, key.PT) == 4 && dv_syn_fits(key.m, key.n, (uint32_t)Ny, B, ell, 4))
-        return false;
+    // With one column a lane it is the faster one with one repetition, 15 columns
+    // and more of at least 960 rows (1366 x 4096, r = 3, 16 columns: 13.8 against
+    // 14.1, over BabyBear 14.4 against 15.0; 1000 x 16000, r = 8: 15.7 and 16.2; 700 x
+    // 700, r = 7: 14.2 and 13.6).
+    const uint32_t cols = dv_decode_cols(key.m, B, key.PT, Yhat, Y, key.PT);
+    const bool many = cols == 4 ? B >= 10 + 3 * ell && (Y || key.cy.r > 1) : Y && ell == 1 && B > 14 && key.m >= 960;
+    if (many && Ny <= kDotFewCols && dv_syn_fits(key.m, key.n, (uint32_t)Ny, B, ell, cols)) return false;
     const uintptr_t y = (uintptr_t)Y, h = (uintptr_t)Yhat, bytes = (uintptr_t)B * key.m * 4;
     if (Y && y < h + bytes && h < y + bytes) return false;  // Y over Yhat: the columns must be read before
     const uint64_t grid = ell * ((Ny + kFusedThreads - 1) / kFusedThreads) + ceil_div(key.n, kCols) +

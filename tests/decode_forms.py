@@ -29,6 +29,12 @@ FORMS = [
     (4096, 2, 15, 1, 31, False, "decode_verify_dot<16, 16>"),
     (4097, 1, 16, 1, 31, False, "decode_verify_dot<16, 16>"),
     (4100, 2, 16, 1, 31, False, "decode_verify_dot<24, 16>"),
+    # one column a lane: 15 columns of at least 960 rows with one repetition
+    (1366, 3, 15, 1, 31, False, "decode_verify_syn<16, 1>"),
+    (960, 8, 16, 1, 31, False, "decode_verify_syn<16, 1>"),
+    (1366, 3, 14, 1, 31, False, "decode_verify_dot<16, 16>"),
+    (959, 8, 16, 1, 31, False, "decode_verify_dot<16, 16>"),
+    (1366, 3, 15, 2, 31, False, "decode_verify_dot<16, 16>"),
     # neither: the syndromes before, in a launch of their own
     (4096, 3, 17, 2, 31, False, "decode_verify_fused"),
 ]
